@@ -161,88 +161,6 @@ __device__ __forceinline__ int s1_window_depth(int64_t n, double tol, int score_
     return (n > S1_MAX_N || d > S1_WIN) ? -1 : max(d, 1);
 }
 
-// guard_mode 1 (Thm 3.4) for one instance that one block finishes: the
-// steps and flags of the single-vector guard stages.  R holds the result of
-// the selection and of the first sweep, S that sweep's sum (units of
-// 2^e_max; 0 when nothing was swept), get(j) the instance's counts over
-// [lo, hi], nz its zero count and sg its sign bits.  Certify, or select the
-// classes again against the certified exponent (put() writes them into the
-// block's class table lut) and let resweep(p, flags) sum the instance again
-// with them, returning (in thread 0) the new sum while it writes value,
-// parts and flags into R; then check again with the larger lower bound.
-// Every thread of the block must call it.
-template <class Get, class Put, class Sweep>
-__device__ void batch_guard(int lo, int hi, unsigned long long nz, unsigned int sg, int64_t n,
-                            double tol, int score_mode, int nonstrict, Get get, Put put,
-                            const unsigned char *lut, double S, qdot_result &R, Sweep &&resweep)
-{
-    __shared__ int s_go, s_dref, s_passes;
-    __shared__ double s_low, s_sum;
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        s_go = R.status == QDOT_OK && R.n_bins > 0;
-        // every product zero: +0 is exact
-        if (R.status == QDOT_OK && R.n_bins == 0) R.flags |= QDOT_F_GUARANTEED;
-        s_dref = 0;
-        s_passes = R.passes;
-    }
-    __syncthreads();
-    if (!s_go) return;
-    const int e_max = R.e_max;
-    const GuardSums g0 = guard_sums<BLOCK>(get, lut, lo, hi, e_max);
-    if (tid == 0) {
-        const double low = guard_lower(g0, S, n, sg);
-        if (guard_certified(R.bound_rel, low, tol)) {
-            R.flags |= QDOT_F_GUARANTEED;
-            R.lower = ldexp(low, e_max);
-        } else {
-            // L <= 0: every bin double (scores >= 23, one more non-strict)
-            const int ref = low > 0.0 ? e_max + ilogb(low) : R.e_min - R.t - 22 - nonstrict;
-            if (ref < e_max) {
-                s_dref = e_max - ref;
-                s_low = low;
-            } else {
-                R.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
-            }
-        }
-    }
-    __syncthreads();
-    if (!s_dref) return;
-    auto noclear = [](int) {};
-    const CutParams p2 = block_cutoff<BLOCK>(lo, hi, nz, 0u, n, tol, score_mode, nonstrict, get,
-                                             put, noclear, &R, nullptr, s_dref);
-    if (tid == 0) {
-        R.flags |= QDOT_F_RESELECTED;
-        R.passes = s_passes + (p2.skip ? 0 : 1);
-        s_sum = 0.0;
-    }
-    __syncthreads();
-    if (!p2.skip) {
-        const double s2 = resweep(p2, p2.flags | QDOT_F_RESELECTED);
-        if (tid == 0) s_sum = s2;
-    }
-    __syncthreads();
-    const GuardSums g1 = guard_sums<BLOCK>(get, lut, lo, hi, e_max);
-    if (tid == 0) {
-        const double low = fmax(guard_lower(g1, s_sum, n, sg), s_low);
-        R.flags |= QDOT_F_RESELECTED |
-                   (guard_certified(R.bound_rel, low, tol) ? QDOT_F_GUARANTEED : 0);
-        R.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
-    }
-    __syncthreads();
-}
-
-// Copies a block's result (LDS) to its slot in device memory (every thread
-// calls it).
-__device__ __forceinline__ void put_result(qdot_result *o, const qdot_result &R)
-{
-    constexpr int NWORD = (int)(sizeof(qdot_result) / sizeof(unsigned long long));
-    static_assert(NWORD * sizeof(unsigned long long) == sizeof(qdot_result), "whole words");
-    if (threadIdx.x < NWORD)
-        reinterpret_cast<unsigned long long *>(o)[threadIdx.x] =
-            reinterpret_cast<const unsigned long long *>(&R)[threadIdx.x];
-}
-
 __device__ __forceinline__ void write_invalid(qdot_result *o)
 {
     o->value = __longlong_as_double(0x7ff8000000000000ll);
@@ -511,7 +429,7 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
                     if (tid == 0) s_first = s0;
                 }
                 __syncthreads();
-                batch_guard(lo, hi, nz, sg, n, tol, score_mode, nonstrict, get, put, lut, s_first,
+                block_guard<BLOCK>(lo, hi, nz, sg, n, tol, score_mode, nonstrict, get, put, lut, s_first,
                             s_res, sweep);
                 put_result(out + inst, s_res);
                 for (int j = lo + tid; j <= hi; j += BLOCK) h[j] = 0u;
@@ -726,7 +644,7 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
                         block_reduce3<BLOCK>(b, red);
                         return tid == 0 ? combine_value(b, cp.e_max, cp.c32, fl, &s_res) : 0.0;
                     };
-                    batch_guard(glo, ghi, gnz, gsg, n, tol, score_mode, nonstrict, get, put, lut,
+                    block_guard<BLOCK>(glo, ghi, gnz, gsg, n, tol, score_mode, nonstrict, get, put, lut,
                                 s_first, s_res, sweep);
                     // a chunk that gave up waiting has marked the instance
                     if (tid == 0 && ld_dev(&out[I.inst].status) == QDOT_E_DEVICE)

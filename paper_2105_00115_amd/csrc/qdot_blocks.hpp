@@ -954,6 +954,91 @@ __device__ __forceinline__ bool guard_certified(double bound_rel, double low, do
     return low > 0.0 && ldexp(bound_rel, -ilogb(low)) <= tol;
 }
 
+// guard_mode 1 (Thm 3.4) for one instance that one block finishes: the
+// steps and flags of the single-vector guard stages.  R holds the result of
+// the selection and of the first sweep, S that sweep's sum (units of
+// 2^e_max; 0 when nothing was swept), get(j) the instance's counts over
+// [lo, hi], nz its zero count and sg its sign bits.  Certify, or select the
+// classes again against the certified exponent (put() writes them into the
+// block's class table lut) and let resweep(p, flags) sum the instance again
+// with them, returning (in thread 0) the new sum while it writes value,
+// parts and flags into R; then check again with the larger lower bound.
+// Every thread of the block must call it.
+template <int NT, class Get, class Put, class Sweep>
+__device__ void block_guard(int lo, int hi, unsigned long long nz, unsigned int sg, int64_t n,
+                            double tol, int score_mode, int nonstrict, Get get, Put put,
+                            const unsigned char *lut, double S, qdot_result &R, Sweep &&resweep,
+                            int mu_single = 0)
+{
+    __shared__ int s_go, s_dref, s_passes;
+    __shared__ double s_low, s_sum;
+    const int tid = threadIdx.x;
+    if (tid == 0) {
+        s_go = R.status == QDOT_OK && R.n_bins > 0;
+        // every product zero: +0 is exact
+        if (R.status == QDOT_OK && R.n_bins == 0) R.flags |= QDOT_F_GUARANTEED;
+        s_dref = 0;
+        s_passes = R.passes;
+    }
+    __syncthreads();
+    if (!s_go) return;
+    const int e_max = R.e_max;
+    const GuardSums g0 = guard_sums<NT>(get, lut, lo, hi, e_max);
+    if (tid == 0) {
+        const double low = guard_lower(g0, S, n, sg);
+        if (guard_certified(R.bound_rel, low, tol)) {
+            R.flags |= QDOT_F_GUARANTEED;
+            R.lower = ldexp(low, e_max);
+        } else {
+            // L <= 0: every bin at the input precision (scores >= 23 for
+            // double inputs, >= 10 for single; one more non-strict)
+            const int ref = low > 0.0 ? e_max + ilogb(low)
+                                      : R.e_min - R.t - (mu_single ? 9 : 22) - nonstrict;
+            if (ref < e_max) {
+                s_dref = e_max - ref;
+                s_low = low;
+            } else {
+                R.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
+            }
+        }
+    }
+    __syncthreads();
+    if (!s_dref) return;
+    auto noclear = [](int) {};
+    const CutParams p2 = block_cutoff<NT>(lo, hi, nz, 0u, n, tol, score_mode, nonstrict, get, put,
+                                          noclear, &R, nullptr, s_dref, mu_single);
+    if (tid == 0) {
+        R.flags |= QDOT_F_RESELECTED;
+        R.passes = s_passes + (p2.skip ? 0 : 1);
+        s_sum = 0.0;
+    }
+    __syncthreads();
+    if (!p2.skip) {
+        const double s2 = resweep(p2, p2.flags | QDOT_F_RESELECTED);
+        if (tid == 0) s_sum = s2;
+    }
+    __syncthreads();
+    const GuardSums g1 = guard_sums<NT>(get, lut, lo, hi, e_max);
+    if (tid == 0) {
+        const double low = fmax(guard_lower(g1, s_sum, n, sg), s_low);
+        R.flags |= QDOT_F_RESELECTED |
+                   (guard_certified(R.bound_rel, low, tol) ? QDOT_F_GUARANTEED : 0);
+        R.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
+    }
+    __syncthreads();
+}
+
+// Copies a block's result (LDS) to its slot in device memory (every thread
+// calls it).
+__device__ __forceinline__ void put_result(qdot_result *o, const qdot_result &R)
+{
+    constexpr int NWORD = (int)(sizeof(qdot_result) / sizeof(unsigned long long));
+    static_assert(NWORD * sizeof(unsigned long long) == sizeof(qdot_result), "whole words");
+    if (threadIdx.x < NWORD)
+        reinterpret_cast<unsigned long long *>(o)[threadIdx.x] =
+            reinterpret_cast<const unsigned long long *>(&R)[threadIdx.x];
+}
+
 // ---- pass 2: leaves of 4 consecutive components ---------------------------
 //
 // Leaves (exact powers of two scale them; the FP64 result is multiplied by

@@ -39,6 +39,21 @@ constexpr int SINGLE_IN = 4;
 constexpr uint64_t FRAC_MASK = 0x000fffffffffffffull;
 constexpr uint64_t ONE_BITS = 0x3ff0000000000000ull;
 
+// Pass-1 counts of the two-launch qdot (qdot_fused.hip): the key slots and,
+// behind them, the zero products, the non-finite ones, and the waves that saw
+// a negative and a positive product, as 32-bit counts in quads of slots.
+constexpr int FH_COPIES = 4;
+constexpr int FH_ZERO = W, FH_BAD = W + 1, FH_NEG = W + 2, FH_POS = W + 3;
+constexpr int FQ = (W + 4) / 4;             // quads of a histogram
+static_assert(W % 4 == 0, "the four counts behind the slots are one quad");
+constexpr int ARRIVE_GROUPS = 8;
+struct FusedWs {
+    uint4 hist[FH_COPIES][FQ];               // zero between calls
+    unsigned int arrive;                     // blocks (or groups) done with the sweep
+    unsigned int pad[31];
+    unsigned int sub[ARRIVE_GROUPS][32];     // one 128-byte line per group
+};
+
 // Control block in device memory, one per handle.
 struct Ws {
     unsigned long long hist[HIST_COPIES][W]; // pass-1 exponent histograms
@@ -64,6 +79,7 @@ struct Ws {
     unsigned int signs;          // OR of block_signs over the last scan
     int g_redo;                  // the reselection ran
     unsigned char lut[W_LUT];    // class of every key slot (+ zero slot)
+    FusedWs fused;
 };
 
 // One-pass (exact per-bin) accumulation: a block keeps candidate sums for
@@ -234,6 +250,60 @@ __device__ __forceinline__ float tile_levels_3to6(float s)
     return s;
 }
 
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned int lo = (unsigned int)dpp_i<CTRL>((int)(b & 0xffffffffll));
+    const unsigned int hi = (unsigned int)dpp_i<CTRL>((int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Lane l's value, in every lane.
+__device__ __forceinline__ int lane_i(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ double lane_d(double v, int l)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned int lo = (unsigned int)lane_i((int)(b & 0xffffffffll), l);
+    const unsigned int hi = (unsigned int)lane_i((int)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Reduction over the wave by a commutative, associative op; the result in
+// every lane.  Four levels of register moves within 16-lane rows, then the
+// four rows' values through scalar registers: a shuffle goes through the LDS
+// crossbar and costs a round trip per level.
+template <class Op>
+__device__ __forceinline__ int wave_reduce_i(int v, Op op)
+{
+    v = op(v, dpp_i<DPP_XOR1>(v));
+    v = op(v, dpp_i<DPP_XOR2>(v));
+    v = op(v, dpp_i<DPP_HALF_MIRROR>(v));
+    v = op(v, dpp_i<DPP_MIRROR>(v));
+    return op(op(lane_i(v, 0), lane_i(v, 16)), op(lane_i(v, 32), lane_i(v, 48)));
+}
+
+// Row rotations: lane i of a 16-lane row takes lane (i + n) mod 16, in lane 0
+// the partner of the xor tree's levels 8, 4, 2, 1.
+constexpr int DPP_FROM8 = 0x128, DPP_FROM4 = 0x12C, DPP_FROM2 = 0x12E, DPP_FROM1 = 0x12F;
+
+// Lane 0: the sum by the xor tree of lane distances 32, 16, ..., 1, its last
+// four levels by row rotations.
+__device__ __forceinline__ double wave_sum_d(double v)
+{
+    v = v + __shfl_xor(v, 32, 64);
+    v = v + __shfl_xor(v, 16, 64);
+    v = v + dpp_d<DPP_FROM8>(v);
+    v = v + dpp_d<DPP_FROM4>(v);
+    v = v + dpp_d<DPP_FROM2>(v);
+    return v + dpp_d<DPP_FROM1>(v);
+}
+
 // ---- compensated FP64 accumulation ---------------------------------------
 struct Acc {
     double s, c;
@@ -269,6 +339,33 @@ __device__ __forceinline__ Acc wave_reduce(Acc a)
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) a = acc_merge(a, acc_shfl_xor(a, m));
     return a;
+}
+
+template <int CTRL>
+__device__ __forceinline__ Acc acc_dpp(Acc a)
+{
+    return acc_merge(a, Acc{dpp_d<CTRL>(a.s), dpp_d<CTRL>(a.c)});
+}
+
+__device__ __forceinline__ Acc lane_acc(Acc a, int l) { return Acc{lane_d(a.s, l), lane_d(a.c, l)}; }
+
+// wave_reduce of accumulators that are zero but in the first lane of each
+// 16-lane row (the merges with zero change nothing): the same pair.
+__device__ __forceinline__ Acc wave_merge_rows(Acc a)
+{
+    return acc_merge(acc_merge(lane_acc(a, 0), lane_acc(a, 32)),
+                     acc_merge(lane_acc(a, 16), lane_acc(a, 48)));
+}
+
+// Lane 0: wave_reduce's pair, its last four levels by row rotations.
+__device__ __forceinline__ Acc wave_reduce_rows(Acc a)
+{
+    a = acc_merge(a, acc_shfl_xor(a, 32));
+    a = acc_merge(a, acc_shfl_xor(a, 16));
+    a = acc_dpp<DPP_FROM8>(a);
+    a = acc_dpp<DPP_FROM4>(a);
+    a = acc_dpp<DPP_FROM2>(a);
+    return acc_dpp<DPP_FROM1>(a);
 }
 
 // ceil(log2 m), m >= 1

@@ -1,0 +1,878 @@
+// The two-pass qdot in two launches (any length), or in one (a length that
+// one block holds in registers).
+//
+// k_key_scan counts the product exponents, as k_scan does.  k_sel_sweep is
+// the selection, the sweep and the combine: every block reads the merged
+// counts and selects the classes itself, into its own LDS table, sums its
+// components, and the last block to finish adds up the blocks' sums, writes
+// the whole result and clears the counts for the next call.  Nothing waits
+// for another block, so the launches need no residency and no fence.
+//
+// A chain of four kernels (scan, selection, sweep, combine) is bound by
+// latency until the vectors are long: on 1e5 components the selection alone,
+// one workgroup of dependent loads and shuffle chains, took 8.4 us and the
+// combine 4.1 us of 26.  Here the counts come in one round trip (whole
+// histograms as 16-byte loads, without finding the live window first), the
+// first group of operands is in flight meanwhile, and a block computes only
+// what its sweep needs (e_max, t and the class of each live slot) before the
+// sweep.  Counts, bound and flags are formed while the block's sums are on
+// their way to memory, and only the last block uses them.  The start-up code
+// runs once per block, so it is bound by instruction fetch: unrolled over the
+// slots of a thread the selection took 1.4 us, as rolled loops over the live
+// slots 0.4 us.
+//
+// Per call, back to back (four kernels -> here): 1000 components 20 -> 11 us
+// (one block, 6.4 us in the kernel), 1e5 24.0 -> 13.8, 1e6 27.5 -> 18.0,
+// guaranteed mode on 1e6 36.6 -> 20.9 (eight launches -> three), 1e7 72.4 ->
+// 62.1, 2^27 695 -> 685, 5e7 floats 168 -> 164.
+//
+// Classes, leaves and tile trees are those of the four-kernel chain, and so is
+// the order of every FP64 sum where the launch shapes are the same (long
+// vectors); on short vectors the compensated sums differ by the rounding of
+// their error terms at most.
+#include "qdot_kernels.hpp"
+
+#include "qdot_blocks.hpp"
+
+namespace qd {
+
+struct FusedArgs {
+    int key_mode, score_mode, nonstrict, mu_single;
+    double tol;
+};
+
+// A block's first group of NT * EPT * U components, loaded into registers
+// ahead of the block's other start-up work.
+template <bool VEC, int U, int NT, class T>
+struct FirstGroup {
+    T xv[U][4], yv[U][4];
+
+    __device__ __forceinline__ static int lim_of(int64_t i0, int64_t n)
+    {
+        const int64_t left = n - i0;
+        return left <= 0 ? 0 : (left >= 4 ? 4 : (int)left);
+    }
+
+    __device__ __forceinline__ void load(const T *__restrict__ x, const T *__restrict__ y,
+                                         int64_t base, int64_t n)
+    {
+        constexpr int64_t chunk = (int64_t)NT * EPT;
+        const bool full = base + chunk * U <= n;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int64_t i0 = base + u * chunk + threadIdx.x * EPT;
+            if (full) {
+                load4_full<VEC>(x + i0, xv[u]);
+                load4_full<VEC>(y + i0, yv[u]);
+            } else {
+                load4_tail(x + i0, lim_of(i0, n), xv[u]);
+                load4_tail(y + i0, lim_of(i0, n), yv[u]);
+            }
+        }
+    }
+
+    // body(xv, yv, lim) on each chunk; the whole group takes lim 4 as a
+    // constant, so that its bounds tests fold away
+    template <class Body>
+    __device__ __forceinline__ void each(int64_t base, int64_t n, Body &&body) const
+    {
+        constexpr int64_t chunk = (int64_t)NT * EPT;
+        if (base + chunk * U <= n) {
+#pragma unroll
+            for (int u = 0; u < U; u++) body(xv[u], yv[u], 4);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                body(xv[u], yv[u], lim_of(base + u * chunk + threadIdx.x * EPT, n));
+        }
+    }
+};
+
+// Counts 4 components into the LDS histogram h; sg collects bit 0 for a
+// negative and bit 1 for a positive non-zero product.
+template <class T>
+__device__ __forceinline__ void count4(const T *xv, const T *yv, int lim, int key_mode,
+                                       unsigned int *h, unsigned int &sg)
+{
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const auto c = [&]() {
+            if constexpr (sizeof(T) == 4) return component_f(xv[e], yv[e], key_mode);
+            else return component(xv[e], yv[e], key_mode);
+        }();
+        const bool valid = e < lim;
+        sg |= (valid & !c.zero) ? (c.sgn ? 1u : 2u) : 0u;
+        // zero products land in FH_ZERO, non-finite ones in FH_BAD
+        if (valid) atomicAdd(&h[c.slot + (c.bad ? 1 : 0)], 1u);
+    }
+}
+
+__device__ __forceinline__ void count_signs(unsigned int sg, unsigned int *h)
+{
+    const bool neg = __ballot(sg & 1u) != 0ull, pos = __ballot(sg & 2u) != 0ull;
+    if ((threadIdx.x & 63) == 0) {
+        if (neg) atomicAdd(&h[FH_NEG], 1u);
+        if (pos) atomicAdd(&h[FH_POS], 1u);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Pass 1: keys into the block's LDS histogram, merged into copy
+// blockIdx % copies of the workspace's counts.
+// ---------------------------------------------------------------------------
+template <class T, bool VEC, int U>
+__global__ __launch_bounds__(BLOCK) void k_key_scan(const T *__restrict__ x,
+                                                    const T *__restrict__ y, int64_t n,
+                                                    int key_mode, Ws *__restrict__ ws, int copies)
+{
+    __shared__ uint4 h4[FQ];
+    unsigned int *h = reinterpret_cast<unsigned int *>(h4);
+    const int64_t group = (int64_t)CHUNK * U;
+    const int64_t stride = group * gridDim.x;
+    const int64_t base = blockIdx.x * group;
+    FirstGroup<VEC, U, BLOCK, T> g;
+    g.load(x, y, base, n);
+    for (int i = threadIdx.x; i < FQ; i += BLOCK) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    unsigned int sg = 0;
+    g.each(base, n, [&](const T *xv, const T *yv, int lim) { count4(xv, yv, lim, key_mode, h, sg); });
+    stream_strided<VEC, U>(x, y, base + stride, stride, n,
+                           [&](const T *xv, const T *yv, int64_t, int lim) {
+                               count4(xv, yv, lim, key_mode, h, sg);
+                           });
+    count_signs(sg, h);
+    __syncthreads();
+    // neighbouring lanes add to neighbouring slots, so that one request
+    // carries a line of them
+    unsigned int *gh = reinterpret_cast<unsigned int *>(ws->fused.hist[blockIdx.x % copies]);
+    for (int i = threadIdx.x; i < 4 * FQ; i += BLOCK) {
+        const unsigned int v = h[i];
+        if (v) atomicAdd(&gh[i], v);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Selection by one block of NT threads from the merged counts, which it holds
+// in LDS (h, 4 FQ words).  Its code runs once per block and cold, so it is
+// kept short: rolled loops over the live slots alone, one slot per lane.
+// ---------------------------------------------------------------------------
+struct Sel {
+    int e_max, e_min, n_bins, t, c32;
+    unsigned int n_zero, bad, signs;
+    __device__ bool live() const { return !bad && n_bins > 0; }
+};
+
+template <int NT>
+struct SelLds {
+    int top, bot, bins;  // highest and lowest live slot, live slots
+    unsigned int cnt[NT / 64][3];
+    double bound[CUT_THREADS / 64];
+    int unatt[NT / 64];
+    double sum;          // S of the combine (units of 2^e_max)
+    int over;            // QDOT_F_OVERFLOW of the combine
+};
+
+// Before find_window, with a barrier between.
+template <int NT>
+__device__ __forceinline__ void select_begin(SelLds<NT> &S)
+{
+    if (threadIdx.x == 0) {
+        S.top = -1;
+        S.bot = W;
+        S.bins = 0;
+    }
+}
+
+// Live slots of the calling thread's quads v (quad k NT + tid is v[k]) into
+// S; a barrier has to follow.
+template <int NT, int K>
+__device__ __forceinline__ void find_window(const uint4 (&v)[K], SelLds<NT> &S)
+{
+    int top = -1, bot = W, bins = 0;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int q = k * NT + (int)threadIdx.x;
+        if (q >= FQ - 1 || !(v[k].x | v[k].y | v[k].z | v[k].w)) continue;
+        top = 4 * q + (v[k].w ? 3 : v[k].z ? 2 : v[k].y ? 1 : 0);
+        bot = min(bot, 4 * q + (v[k].x ? 0 : v[k].y ? 1 : v[k].z ? 2 : 3));
+        bins += (v[k].x ? 1 : 0) + (v[k].y ? 1 : 0) + (v[k].z ? 1 : 0) + (v[k].w ? 1 : 0);
+    }
+    // few waves hold live slots
+    if (__ballot(bins) != 0ull) {
+        top = wave_reduce_i(top, [](int p, int r) { return max(p, r); });
+        bot = wave_reduce_i(bot, [](int p, int r) { return min(p, r); });
+        bins = wave_reduce_i(bins, [](int p, int r) { return p + r; });
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&S.top, top);
+            atomicMin(&S.bot, bot);
+            atomicAdd(&S.bins, bins);
+        }
+    }
+}
+
+__device__ __forceinline__ int sigma_of(unsigned int m, int slot, const Sel &s)
+{
+    // eq. (bin-score-def) with exact bins
+    const int cl = m <= 1u ? 0 : 32 - __clz((int)(m - 1u));
+    return cl + slot + KMIN - s.e_max - s.t + 1;
+}
+
+__device__ __forceinline__ int sel_class(int sigma, int nonstrict, int mu_single)
+{
+    const int c = class_of(sigma, nonstrict);
+    return mu_single && c == QDOT_DOUBLE ? SINGLE_IN : c;
+}
+
+// e_max, e_min, N_bins and t from the window in S, and the classes of the
+// slots in it (perforated where empty) and of the zero slot into lut: the
+// only ones that a component can have.  Every thread calls it, after a
+// barrier that completes h and the window; it ends with one.
+template <int NT>
+__device__ __forceinline__ Sel select_classes(const unsigned int *h, const FusedArgs &a,
+                                              const SelLds<NT> &S, unsigned char *lut)
+{
+    const int tid = threadIdx.x;
+    const int top = S.top, bot = S.bot;
+    Sel s;
+    s.n_bins = S.bins;
+    s.e_max = top + KMIN;
+    s.e_min = bot + KMIN;
+    s.t = s.n_bins
+              ? floor_log2_ratio(a.tol, a.score_mode == 0 ? (unsigned long long)s.n_bins : 1ull)
+              : 0;
+    s.c32 = s.e_max + s.t + 22;
+    s.n_zero = h[FH_ZERO];
+    s.bad = h[FH_BAD];
+    s.signs = (h[FH_NEG] ? 1u : 0u) | (h[FH_POS] ? 2u : 0u);
+#pragma unroll 1
+    for (int j = bot + tid; j <= top; j += NT) {
+        const unsigned int m = h[j];
+        const int cls = sel_class(sigma_of(m, j, s), a.nonstrict, a.mu_single);
+        lut[j] = (unsigned char)(m ? cls : QDOT_PERF);
+    }
+    if (tid == 0) lut[ZERO_SLOT] = (unsigned char)QDOT_PERF;
+    __syncthreads();
+    return s;
+}
+
+// Counts per class, the bound's sums and the unattainable flag into S.  The
+// bound is summed in block_cutoff's order (that of a workgroup of CUT_THREADS
+// threads, one slot per thread from the lowest live one), so it is the same
+// bit for bit: wave by wave of 64 slots, and the waves' sums in finish_result.
+// Every thread calls it; a barrier has to follow.
+template <int NT>
+__device__ __forceinline__ void select_count(const unsigned int *h, const Sel &s,
+                                             const FusedArgs &a, SelLds<NT> &S)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int cd = 0, cs = 0, ch = 0, unatt = 0;
+    const int ulim = (a.mu_single ? 23 : 52) + (a.nonstrict ? 1 : 0);
+    const int bot = s.e_min - KMIN, top = s.e_max - KMIN;
+#pragma unroll 1
+    for (int w = wv; w < CUT_THREADS / 64; w += NT / 64) {
+        double bound = 0.0;
+#pragma unroll 1
+        for (int j = bot + w * 64 + lane; j <= top; j += CUT_THREADS) {
+            const unsigned int m = h[j];
+            if (!m) continue;
+            const int sigma = sigma_of(m, j, s);
+            const int cls = sel_class(sigma, a.nonstrict, a.mu_single);
+            unatt |= sigma >= ulim;
+            cd += cls == QDOT_DOUBLE ? (int)m : 0;
+            cs += (cls == QDOT_SINGLE || cls == SINGLE_IN) ? (int)m : 0;
+            ch += cls == QDOT_HALF ? (int)m : 0;
+            // Thm 3.3 term M_k 2^(k - e_max + 1) eps(class)
+            bound += ldexp((double)m * eps_of_class(cls), j + KMIN - s.e_max + 1);
+        }
+        if (bot + w * 64 <= top) bound = wave_sum_d(bound);
+        if (lane == 0) S.bound[w] = bound;
+    }
+    auto add = [](int p, int r) { return p + r; };
+    cd = wave_reduce_i(cd, add);
+    cs = wave_reduce_i(cs, add);
+    ch = wave_reduce_i(ch, add);
+    const bool ua = __ballot(unatt) != 0ull;
+    if (lane == 0) {
+        S.cnt[wv][0] = (unsigned int)cd;
+        S.cnt[wv][1] = (unsigned int)cs;
+        S.cnt[wv][2] = (unsigned int)ch;
+        S.unatt[wv] = ua;
+    }
+}
+
+// The whole result into R: wave 0 finishes select_count's sums (counts,
+// bounds and flags as block_cutoff forms them), wave 1 the class sums (red,
+// per wave, as block_reduce3_waves leaves them) with combine_value, both at
+// the same time.  Every thread calls it, after a barrier; it ends with one.
+// The sum before scaling is left in S.sum (0 when nothing was kept).
+template <int NT>
+__device__ __forceinline__ void finish_result(const Sel &s, const FusedArgs &a, int64_t n,
+                                              SelLds<NT> &S, Acc (*red)[NT / 64], qdot_result &R)
+{
+    constexpr int NW = NT / 64;
+    const int tid = threadIdx.x;
+    if (tid == 0) {
+        long long c[3] = {0, 0, 0};
+        double b = 0.0;
+        int u = 0;
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            for (int q = 0; q < 3; q++) c[q] += S.cnt[w][q];
+            u |= S.unatt[w];
+        }
+#pragma unroll
+        for (int w = 0; w < CUT_THREADS / 64; w++) b += S.bound[w];
+        const bool live = s.live(), bad = s.bad != 0;
+        const bool none = c[0] + c[1] + c[2] == 0;
+        int flags = u ? QDOT_F_UNATTAINABLE : 0;
+        // Thm 3.6, as in block_cutoff
+        if ((long long)s.e_max - s.e_min <= -(long long)s.t - (a.mu_single ? 10 : 23))
+            flags |= QDOT_F_THM_ALL_DOUBLE;
+        if (none) flags |= QDOT_F_ALL_PERF;
+        // an error result: status and a NaN value, every other field 0
+        R.status = bad ? QDOT_E_NONFINITE : QDOT_OK;
+        R.n_zero = bad ? 0 : s.n_zero;
+        R.n_bins = live ? s.n_bins : 0;
+        R.e_max = R.e_ref = live ? s.e_max : 0;
+        R.e_min = live ? s.e_min : 0;
+        R.t = live ? s.t : 0;
+        R.count[QDOT_DOUBLE] = live ? c[0] : 0;
+        R.count[QDOT_SINGLE] = live ? c[1] : 0;
+        R.count[QDOT_HALF] = live ? c[2] : 0;
+        R.count[QDOT_PERF] = bad ? 0 : live ? n - c[0] - c[1] - c[2] : n;
+        R.bound_rel = live ? b : 0.0;
+        R.bound_abs = live ? ldexp(b, s.e_max) : 0.0;
+        R.lower = 0.0;
+        R.passes = live && !none ? 1 : 0;
+        R.flags = bad ? 0 : live ? flags : QDOT_F_ALL_PERF;
+    }
+    if (tid >> 6 == 1) {
+        // one lane per class, then the three together
+        const int lane = tid & 63, q = lane < 3 ? lane : 0;
+        Acc b = red[q][0];
+#pragma unroll
+        for (int w = 1; w < NW; w++) b = acc_merge(b, red[q][w]);
+        Acc f[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) f[c] = Acc{__shfl(b.s, c, 64), __shfl(b.c, c, 64)};
+        if (lane == 0) {
+            qdot_result V;
+            double sum = 0.0;
+            V.value = 0.0;
+            V.part[0] = V.part[1] = V.part[2] = 0.0;
+            V.flags = 0;
+            if (s.live()) sum = combine_value(f, s.e_max, s.c32, 0, &V, a.mu_single);
+            // an error result has a NaN value
+            R.value = s.bad ? __longlong_as_double(0x7ff8000000000000ll) : V.value;
+            for (int c = 0; c < 3; c++) R.part[c] = V.part[c];
+            S.sum = sum;
+            S.over = V.flags;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) R.flags |= S.over;
+    __syncthreads();
+}
+
+// Per-wave sums of three accumulators into red (a barrier has to follow).
+// The FP32 classes' accumulators are held by the first lane of each 16-lane
+// row alone (acc_group), unless ALL.
+template <int NT, bool ALL>
+__device__ __forceinline__ void block_reduce3_waves(Acc a[3], Acc (*red)[NT / 64])
+{
+    a[0] = wave_reduce_rows(a[0]);
+#pragma unroll
+    for (int q = 1; q < 3; q++) {
+        a[q] = ALL ? wave_reduce_rows(a[q]) : wave_merge_rows(a[q]);
+    }
+    if ((threadIdx.x & 63) == 0)
+        for (int q = 0; q < 3; q++) red[q][threadIdx.x >> 6] = a[q];
+}
+
+// Counts this block as done with its sweep; true in every thread of the
+// last of nblk blocks.  What the block stored before with device-scope
+// stores is complete when it counts itself, so the last block sees it with
+// device-scope loads.  Past 64 blocks they count in two levels, so that no
+// counter takes more than nblk / 8 atomics in a row.  The counters are zero
+// again afterwards.
+__device__ __forceinline__ bool last_block(FusedWs &F, int blk, int nblk)
+{
+    __shared__ int s_last;
+    if (threadIdx.x == 0) {
+        vmem_drain();
+        bool last = true;
+        unsigned int all = (unsigned int)nblk;
+        if (nblk > 64) {
+            const int g = blk % ARRIVE_GROUPS;
+            const unsigned int members =
+                (unsigned int)((nblk - g + ARRIVE_GROUPS - 1) / ARRIVE_GROUPS);
+            last = __hip_atomic_fetch_add(&F.sub[g][0], 1u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT) + 1 == members;
+            if (last) st_dev(&F.sub[g][0], 0u);
+            all = ARRIVE_GROUPS;
+        }
+        if (last)
+            last = __hip_atomic_fetch_add(&F.arrive, 1u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT) + 1 == all;
+        if (last) st_dev(&F.arrive, 0u);
+        s_last = last;
+    }
+    __syncthreads();
+    return s_last != 0;
+}
+
+// A block's sums: lanes 0..2 merge the waves' of one class each and store them
+// (partials as six rows of nblk words, which the last block reads in whole
+// lines).  A barrier precedes it.
+__device__ __forceinline__ void store_partial(double *partials, int blk, int nblk,
+                                              Acc (*red)[BLOCK / 64])
+{
+    const int q = threadIdx.x;
+    if (q < 3) {
+        Acc b = red[q][0];
+#pragma unroll
+        for (int w = 1; w < BLOCK / 64; w++) b = acc_merge(b, red[q][w]);
+        st_dev(&partials[(size_t)(2 * q) * nblk + blk], b.s);
+        st_dev(&partials[(size_t)(2 * q + 1) * nblk + blk], b.c);
+    }
+}
+
+// The blocks' sums merged in a fixed order, per wave into red (a barrier has
+// to follow).  Two blocks' sums are in flight per thread.
+__device__ __forceinline__ void merge_partials(const double *partials, int nblk,
+                                               Acc (*red)[BLOCK / 64])
+{
+    constexpr int P = 2;
+    Acc f[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    for (int b0 = threadIdx.x; b0 < nblk; b0 += P * BLOCK) {
+        Acc p[P][3];
+#pragma unroll
+        for (int u = 0; u < P; u++) {
+            const int b = b0 + u * BLOCK;
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                p[u][q] = Acc{0.0, 0.0};
+                if (b < nblk)
+                    p[u][q] = Acc{ld_dev(&partials[(size_t)(2 * q) * nblk + b]),
+                                  ld_dev(&partials[(size_t)(2 * q + 1) * nblk + b])};
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < P; u++)
+#pragma unroll
+            for (int q = 0; q < 3; q++) f[q] = acc_merge(f[q], p[u][q]);
+    }
+    block_reduce3_waves<BLOCK, true>(f, red);
+}
+
+// ---------------------------------------------------------------------------
+// Selection, sweep and combine of one product by blocks blk of nblk.
+// GUARD (guard_mode 1): the last block also certifies the result, or selects
+// the classes again and leaves them, the counts and g_redo to k_resweep.
+// ---------------------------------------------------------------------------
+template <class T, bool VEC, int U, bool GUARD>
+__device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__restrict__ y,
+                                          int64_t n, const FusedArgs &a, Ws *__restrict__ ws,
+                                          int copies, double *__restrict__ partials,
+                                          qdot_result *__restrict__ out, int blk, int nblk)
+{
+    constexpr int K = (FQ + BLOCK - 1) / BLOCK;
+    __shared__ uint4 h4[FQ];
+    __shared__ SelLds<BLOCK> S;
+    __shared__ unsigned char lut[W_LUT];
+    __shared__ Acc red[3][BLOCK / 64];
+    __shared__ qdot_result R;
+    const unsigned int *h = reinterpret_cast<const unsigned int *>(h4);
+    const int tid = threadIdx.x;
+    FusedWs &F = ws->fused;
+
+    uint4 v[K];
+    {
+        auto quad = [&](int c, int k) {
+            const int q = k * BLOCK + tid;
+            return q < FQ ? F.hist[c][q] : make_uint4(0u, 0u, 0u, 0u);
+        };
+        auto plus = [](uint4 p, uint4 r) {
+            return make_uint4(p.x + r.x, p.y + r.y, p.z + r.z, p.w + r.w);
+        };
+        if (copies == 1) {
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = quad(0, k);
+        } else if (copies == 2) {
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = plus(quad(0, k), quad(1, k));
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; k++)
+                v[k] = plus(plus(quad(0, k), quad(1, k)), plus(quad(2, k), quad(3, k)));
+        }
+    }
+
+    const int64_t group = (int64_t)CHUNK * U;
+    const int64_t stride = group * nblk;
+    const int64_t base = blk * group;
+    FirstGroup<VEC, U, BLOCK, T> g;
+    g.load(x, y, base, n);
+    select_begin(S);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; k++)
+        if (k * BLOCK + tid < FQ) h4[k * BLOCK + tid] = v[k];
+    find_window<BLOCK, K>(v, S);
+    __syncthreads();
+    const Sel s = select_classes<BLOCK>(h, a, S, lut);
+    Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    if (s.live()) {
+        auto leaves = [&](const T *xv, const T *yv, int lim) {
+            acc_group<false>(xv, yv, lim, lut, a.key_mode, s.e_max, s.c32, true, acc[0], acc[1],
+                             acc[2], nullptr);
+        };
+        g.each(base, n, leaves);
+        stream_strided<VEC, U>(
+            x, y, base + stride, stride, n,
+            [&](const T *xv, const T *yv, int64_t, int lim) { leaves(xv, yv, lim); });
+    }
+    block_reduce3_waves<BLOCK, false>(acc, red);
+    __syncthreads();
+    store_partial(partials, blk, nblk, red);
+    // only the last block needs them; here they cost it nothing, while its
+    // sums are on their way to memory
+    select_count<BLOCK>(h, s, a, S);
+    if (!last_block(F, blk, nblk)) return;
+
+    // the last block: the result, and the counts zero for the next call
+    merge_partials(partials, nblk, red);
+    for (int c = 0; c < copies; c++)
+        for (int i = tid; i < FQ; i += BLOCK) F.hist[c][i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    finish_result<BLOCK>(s, a, n, S, red, R);
+    if constexpr (GUARD) {
+        __shared__ int s_dref;
+        const int lo = s.n_bins ? s.e_min - KMIN : W, hi = s.n_bins ? s.e_max - KMIN : -1;
+        const bool go = s.live();
+        GuardSums gs = {0.0, 0.0, 0.0};
+        if (go) gs = guard_sums<BLOCK>([&](int j) { return h[j]; }, lut, lo, hi, s.e_max);
+        if (tid == 0) {
+            s_dref = 0;
+            ws->g_redo = 0;
+            // every product zero: +0 is exact
+            if (!s.bad && s.n_bins == 0) R.flags |= QDOT_F_GUARANTEED;
+            if (go) {
+                const double low = guard_lower(gs, S.sum, n, s.signs);
+                if (guard_certified(R.bound_rel, low, a.tol)) {
+                    R.flags |= QDOT_F_GUARANTEED;
+                    R.lower = ldexp(low, s.e_max);
+                } else {
+                    // L <= 0: every bin at the input precision (scores >= 23
+                    // for double inputs, >= 10 for single; one more
+                    // non-strict)
+                    const int ref = low > 0.0 ? s.e_max + ilogb(low)
+                                              : s.e_min - s.t - (a.mu_single ? 9 : 22) - a.nonstrict;
+                    if (ref < s.e_max) {
+                        s_dref = s.e_max - ref;
+                        ws->g_low = low;
+                        ws->g_redo = 1;
+                    } else {
+                        R.lower = low > 0.0 ? ldexp(low, s.e_max) : 0.0;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (s_dref) {
+            const int passes = R.passes;
+            __syncthreads();
+            // k_resweep certifies with the same counts
+            for (int j = lo + tid; j <= hi; j += BLOCK) ws->hsave[j] = h[j];
+            auto get = [&](int j) { return (unsigned long long)h[j]; };
+            auto put = [&](int j, int cls) { ws->lut[j] = (unsigned char)cls; };
+            auto clear = [](int) {};
+            const CutParams p =
+                block_cutoff<BLOCK>(lo, hi, s.n_zero, 0u, n, a.tol, a.score_mode, a.nonstrict,
+                                    get, put, clear, &R, nullptr, s_dref, a.mu_single);
+            if (tid < W_LUT - W) ws->lut[W + tid] = (unsigned char)QDOT_PERF;
+            if (tid == 0) {
+                ws->e_max = s.e_max;
+                ws->c32 = p.c32;
+                ws->flags = p.flags | QDOT_F_RESELECTED;
+                ws->skip = p.skip;
+                ws->s1_lo = lo;
+                ws->s1_hi = hi;
+                ws->signs = s.signs;
+                R.flags |= QDOT_F_RESELECTED;
+                R.passes = passes + (p.skip ? 0 : 1);
+            }
+        }
+    }
+    __syncthreads();
+    put_result(out, R);
+}
+
+template <class T, bool VEC, int U, bool GUARD>
+__global__ __launch_bounds__(BLOCK, GUARD ? 1 : 4) void k_sel_sweep(const T *__restrict__ x,
+                                                     const T *__restrict__ y, int64_t n,
+                                                     FusedArgs a, Ws *__restrict__ ws, int copies,
+                                                     double *__restrict__ partials,
+                                                     qdot_result *__restrict__ out)
+{
+    sel_sweep<T, VEC, U, GUARD>(x, y, n, a, ws, copies, partials, out, blockIdx.x, gridDim.x);
+}
+
+// Guaranteed mode, after a reselection (g_redo): the second sweep with the
+// classes in the workspace, its combine, and the check with the larger lower
+// bound.  Returns at once when the first selection stood.
+template <class T, bool VEC, int U>
+__global__ __launch_bounds__(BLOCK) void k_resweep(const T *__restrict__ x,
+                                                   const T *__restrict__ y, int64_t n,
+                                                   FusedArgs a, Ws *__restrict__ ws,
+                                                   double *__restrict__ partials,
+                                                   qdot_result *__restrict__ out)
+{
+    __shared__ unsigned int lut32[W_LUT / 4];
+    __shared__ Acc red[3][BLOCK / 64];
+    __shared__ qdot_result R;
+    if (!ws->g_redo) return;
+    const unsigned char *lut = reinterpret_cast<const unsigned char *>(lut32);
+    const int tid = threadIdx.x;
+    const int e_max = ws->e_max, c32 = ws->c32, skip = ws->skip;
+    for (int i = tid; i < W_LUT / 4; i += BLOCK)
+        lut32[i] = reinterpret_cast<const unsigned int *>(ws->lut)[i];
+    __syncthreads();
+    Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    if (!skip)
+        stream_groups<VEC, U>(x, y, n, [&](const T *xv, const T *yv, int64_t, int lim) {
+            acc_group<false>(xv, yv, lim, lut, a.key_mode, e_max, c32, true, acc[0], acc[1],
+                             acc[2], nullptr);
+        });
+    block_reduce3_waves<BLOCK, false>(acc, red);
+    __syncthreads();
+    store_partial(partials, blockIdx.x, gridDim.x, red);
+    if (!last_block(ws->fused, blockIdx.x, gridDim.x)) return;
+    merge_partials(partials, gridDim.x, red);
+    const GuardSums g = guard_sums<BLOCK>([&](int j) { return ws->hsave[j]; }, lut, ws->s1_lo,
+                                          ws->s1_hi, e_max);
+    __syncthreads();
+    if (tid == 0) {
+        R = *out;
+        Acc f[3];
+        for (int q = 0; q < 3; q++) {
+            f[q] = red[q][0];
+            for (int w = 1; w < BLOCK / 64; w++) f[q] = acc_merge(f[q], red[q][w]);
+        }
+        const double sum =
+            skip ? 0.0 : combine_value(f, e_max, c32, ws->flags, &R, a.mu_single);
+        const double low = fmax(guard_lower(g, sum, n, ws->signs), ws->g_low);
+        R.flags |= QDOT_F_RESELECTED |
+                   (guard_certified(R.bound_rel, low, a.tol) ? QDOT_F_GUARANTEED : 0);
+        R.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
+    }
+    __syncthreads();
+    put_result(out, R);
+}
+
+// ---------------------------------------------------------------------------
+// The whole qdot by one block that keeps its components in registers: n <=
+// 4 NT U.
+// ---------------------------------------------------------------------------
+template <class T, bool VEC, int U, int NT, bool GUARD>
+__global__ __launch_bounds__(NT) void k_qdot_block(const T *__restrict__ x,
+                                                   const T *__restrict__ y, int64_t n,
+                                                   FusedArgs a, qdot_result *__restrict__ out)
+{
+    constexpr int K = (FQ + NT - 1) / NT;
+    __shared__ uint4 h4[FQ];
+    __shared__ SelLds<NT> S;
+    __shared__ unsigned char lut[W_LUT];
+    __shared__ Acc red[3][NT / 64];
+    __shared__ qdot_result R;
+    unsigned int *h = reinterpret_cast<unsigned int *>(h4);
+    const int tid = threadIdx.x;
+    FirstGroup<VEC, U, NT, T> g;
+    g.load(x, y, 0, n);
+    for (int i = tid; i < FQ; i += NT) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+    select_begin(S);
+    __syncthreads();
+    unsigned int sg = 0;
+    g.each(0, n, [&](const T *xv, const T *yv, int lim) { count4(xv, yv, lim, a.key_mode, h, sg); });
+    count_signs(sg, h);
+    __syncthreads();
+    uint4 v[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int q = k * NT + tid;
+        v[k] = q < FQ ? h4[q] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    find_window<NT, K>(v, S);
+    __syncthreads();
+    const Sel s = select_classes<NT>(h, a, S, lut);
+    auto sweep = [&](int e_max, int c32, Acc acc[3]) {
+        for (int q = 0; q < 3; q++) acc[q] = Acc{0.0, 0.0};
+        g.each(0, n, [&](const T *xv, const T *yv, int lim) {
+            acc_group<false>(xv, yv, lim, lut, a.key_mode, e_max, c32, true, acc[0], acc[1],
+                             acc[2], nullptr);
+        });
+        block_reduce3_waves<NT, false>(acc, red);
+        __syncthreads();
+    };
+    Acc acc[3];
+    select_count<NT>(h, s, a, S);
+    if (s.live()) sweep(s.e_max, s.c32, acc);
+    else __syncthreads();
+    finish_result<NT>(s, a, n, S, red, R);
+    if constexpr (GUARD) {
+        const int lo = s.n_bins ? s.e_min - KMIN : W, hi = s.n_bins ? s.e_max - KMIN : -1;
+        auto get = [&](int j) { return (unsigned long long)h[j]; };
+        auto put = [&](int j, int c) { lut[j] = (unsigned char)c; };
+        block_guard<NT>(
+            lo, hi, s.n_zero, s.signs, n, a.tol, a.score_mode, a.nonstrict, get, put, lut, S.sum, R,
+            [&](const CutParams &p, int flags) {
+                Acc b[3];
+                sweep(p.e_max, p.c32, b);
+                if (tid != 0) return 0.0;
+                for (int q = 0; q < 3; q++) {
+                    b[q] = red[q][0];
+                    for (int w = 1; w < NT / 64; w++) b[q] = acc_merge(b[q], red[q][w]);
+                }
+                return combine_value(b, p.e_max, p.c32, flags, &R, a.mu_single);
+            },
+            a.mu_single);
+    }
+    __syncthreads();
+    put_result(out, R);
+}
+
+// ---------------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------------
+template <int U>
+static int fused_grid(int64_t n, int cap)
+{
+    const int64_t groups = (n + (int64_t)CHUNK * U - 1) / ((int64_t)CHUNK * U);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(cap, groups));
+}
+
+// Copies of the counts that the scan's blocks spread over: the adds of one
+// slot queue at its address, and every block of the sweep reads every copy.
+// On 98 blocks 2 and 4 copies took the same time, on 256 to 512 four were
+// 0.5 to 2 us faster than two.
+static int fused_copies(int grid) { return grid <= 64 ? 1 : FH_COPIES; }
+
+// Pass 1; returns the copies of the counts that it used.
+template <class T, bool VEC, int U>
+static int launch_key_scan(const Launch &L, const T *x, const T *y, int64_t n, int key_mode)
+{
+    const int grid = fused_grid<U>(n, L.scan_blocks), copies = fused_copies(grid);
+    hipLaunchKernelGGL((k_key_scan<T, VEC, U>), dim3(grid), dim3(BLOCK), 0, L.stream, x, y, n,
+                       key_mode, L.ws, copies);
+    return copies;
+}
+
+template <class T, bool VEC, int U>
+static void launch_sel_sweep(const Launch &L, const T *x, const T *y, int64_t n,
+                             const FusedArgs &a, int copies, int guard, qdot_result *out)
+{
+    const dim3 grid(fused_grid<U>(n, L.acc_blocks));
+    if (guard) {
+        hipLaunchKernelGGL((k_sel_sweep<T, VEC, U, true>), grid, dim3(BLOCK), 0, L.stream, x, y,
+                           n, a, L.ws, copies, L.partials, out);
+        hipLaunchKernelGGL((k_resweep<T, VEC, U>), grid, dim3(BLOCK), 0, L.stream, x, y, n, a,
+                           L.ws, L.partials, out);
+    } else {
+        hipLaunchKernelGGL((k_sel_sweep<T, VEC, U, false>), grid, dim3(BLOCK), 0, L.stream, x, y,
+                           n, a, L.ws, copies, L.partials, out);
+    }
+}
+
+template <class T, bool VEC, int U, int NT>
+static void launch_block_u(const Launch &L, const T *x, const T *y, int64_t n,
+                           const FusedArgs &a, int guard, qdot_result *out)
+{
+    if (guard)
+        hipLaunchKernelGGL((k_qdot_block<T, VEC, U, NT, true>), dim3(1), dim3(NT), 0, L.stream, x,
+                           y, n, a, out);
+    else
+        hipLaunchKernelGGL((k_qdot_block<T, VEC, U, NT, false>), dim3(1), dim3(NT), 0, L.stream, x,
+                           y, n, a, out);
+}
+
+// One block takes a vector of one group of 1024 threads: on 4000 components
+// it took 11.6 us against 14.2 in two launches (and 11.5 against 20.3 in four
+// on 1000); on 8000, two groups, 17.1 against 14.2, one CU's arithmetic.
+constexpr int64_t ONE_BLOCK_MAX = 4096;
+// Up to this length every chunk gets a block of its own: on 3e5 components
+// 15.7 us, against 17.5 with four chunks per block in flight (floats 16.3
+// against 22.5).
+constexpr int64_t WIDE_MAX = (int64_t)CHUNK * 512;
+
+template <class T, bool VEC>
+static void launch_fused_v(const Launch &L, const T *x, const T *y, int64_t n,
+                           const FusedArgs &a, int guard, qdot_result *out)
+{
+    if (n <= ONE_BLOCK_MAX) {
+        if (n <= 1024) launch_block_u<T, VEC, 1, 256>(L, x, y, n, a, guard, out);
+        else launch_block_u<T, VEC, 1, 1024>(L, x, y, n, a, guard, out);
+        if (L.ev) {
+            (void)hipEventRecord(L.ev[1], L.stream);
+            (void)hipEventRecord(L.ev[2], L.stream);
+        }
+        return;
+    }
+    // longer vectors take the tuned groups in flight (twice as many for floats)
+    const int f = sizeof(T) == 4 ? 2 : 1;
+    const bool wide = n <= WIDE_MAX;
+    const int us = wide ? 1 : std::min(4, f * L.scan_unroll);
+    const int ua = wide ? 1 : std::min(4, f * L.acc_unroll);
+    const int copies = us == 1   ? launch_key_scan<T, VEC, 1>(L, x, y, n, a.key_mode)
+                       : us == 2 ? launch_key_scan<T, VEC, 2>(L, x, y, n, a.key_mode)
+                                 : launch_key_scan<T, VEC, 4>(L, x, y, n, a.key_mode);
+    if (L.ev) {
+        (void)hipEventRecord(L.ev[1], L.stream);
+        (void)hipEventRecord(L.ev[2], L.stream);
+    }
+    // (four groups of doubles ahead of the selection would spill)
+    if (ua == 1) launch_sel_sweep<T, VEC, 1>(L, x, y, n, a, copies, guard, out);
+    else if (ua == 2 || sizeof(T) == 8)
+        launch_sel_sweep<T, VEC, 2>(L, x, y, n, a, copies, guard, out);
+    else if constexpr (sizeof(T) == 4)
+        launch_sel_sweep<T, VEC, 4>(L, x, y, n, a, copies, guard, out);
+}
+
+template <class T>
+static hipError_t launch_fused_t(const Launch &L, const T *x, const T *y, int64_t n, double tol,
+                                 const qdot_options &o, qdot_result *out)
+{
+    const bool vec = ((((uintptr_t)x) | ((uintptr_t)y)) & 15) == 0;
+    const FusedArgs a = {o.key_mode, o.score_mode, o.boundary_mode, sizeof(T) == 4 ? 1 : 0, tol};
+    if (L.ev) (void)hipEventRecord(L.ev[0], L.stream);
+    if (vec) launch_fused_v<T, true>(L, x, y, n, a, o.guard_mode, out);
+    else launch_fused_v<T, false>(L, x, y, n, a, o.guard_mode, out);
+    if (L.ev) {
+        (void)hipEventRecord(L.ev[3], L.stream);
+        (void)hipEventRecord(L.ev[4], L.stream);
+    }
+    return hipGetLastError();
+}
+
+bool fused_ok(const Launch &L, int64_t n, const qdot_options &o)
+{
+    // 32-bit counts; the tuned variants of the four-kernel chain (threads per
+    // block, compacting sweep) and its other selections stay there.  Tile keys
+    // save reads, which bound long vectors only: on 2^20 components the chain
+    // took the same time with and without them.
+    return n < ((int64_t)1 << 31) && o.accum_mode == 0 && o.bin_mode == 0 &&
+           (!L.tiles || n <= WIDE_MAX) && L.acc_form == 0 && L.block_threads == BLOCK;
+}
+
+hipError_t launch_fused(const Launch &L, const double *x, const double *y, int64_t n, double tol,
+                        const qdot_options &o, qdot_result *out)
+{
+    return launch_fused_t<double>(L, x, y, n, tol, o, out);
+}
+
+hipError_t launch_fused(const Launch &L, const float *x, const float *y, int64_t n, double tol,
+                        const qdot_options &o, qdot_result *out)
+{
+    return launch_fused_t<float>(L, x, y, n, tol, o, out);
+}
+
+}  // namespace qd

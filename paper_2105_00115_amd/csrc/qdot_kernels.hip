@@ -873,6 +873,8 @@ static hipError_t launch_qdot_t(const Launch &L, const T *x, const T *y, int64_t
                                 unsigned char *cls_out, long long *hist_out,
                                 int nscan_pre = -1)
 {
+    if (nscan_pre < 0 && !cls_out && !hist_out && fused_ok(L, n, o))
+        return launch_fused(L, x, y, n, tol, o, out);
     const bool vec = ((((uintptr_t)x) | ((uintptr_t)y)) & 15) == 0;
     const int guard = o.guard_mode;
     const int mu_single = sizeof(T) == 4 ? 1 : 0;

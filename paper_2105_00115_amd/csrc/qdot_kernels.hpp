@@ -55,6 +55,14 @@ hipError_t launch_qdot_f32(const Launch &L, const float *x, const float *y, int6
                            double tol, const qdot_options &o, qdot_result *out,
                            unsigned char *cls_out, long long *hist_out);
 
+// The same two-pass qdot in two launches, or in one for a short vector
+// (qdot_fused.hip), for the calls that fused_ok() admits.
+bool fused_ok(const Launch &L, int64_t n, const qdot_options &o);
+hipError_t launch_fused(const Launch &L, const double *x, const double *y, int64_t n, double tol,
+                        const qdot_options &o, qdot_result *out);
+hipError_t launch_fused(const Launch &L, const float *x, const float *y, int64_t n, double tol,
+                        const qdot_options &o, qdot_result *out);
+
 // Enqueue the plain FP64 dot; *out receives sum x_i y_i.
 hipError_t launch_dot64(const Launch &L, const double *x, const double *y, int64_t n,
                         double *out);

@@ -1,0 +1,89 @@
+"""The two-pass qdot in two launches, and in one block, at the lengths where
+their dispatch and their groups end, against the oracle; and against the
+four-kernel chain, which other launch shapes still take."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2105_00115_amd as q
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("count", "n_zero", "e_min", "e_max", "n_bins", "t", "flags", "status", "e_ref",
+          "passes")
+# one block: a chunk of 256 threads (1024), of 1024 threads (4096); past it
+# one block per chunk up to 512 chunks, then several chunks per block; one
+# copy of the counts up to 64 blocks (65536)
+SIZES = [0, 1, 3, 4, 63, 65, 1023, 1024, 1025, 4095, 4096, 4097, 65535, 65537, 524288, 524289,
+         1 << 20, (1 << 20) + 7]
+
+
+@pytest.fixture(scope="module")
+def h():
+    handle = q.Qdot(0)
+    yield handle
+    handle.close()
+
+
+def _pair(n, seed, dtype, off):
+    import torch
+    x, y = workloads.log_uniform_pair(n + off, seed)
+    if n > 8:  # a zero product and a subnormal operand
+        x[off + n // 2] = 0.0
+        y[off + n // 3] = 5e-310 if dtype == np.float64 else 1e-42
+    x, y = x.astype(dtype), y.astype(dtype)
+    xd, yd = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(y).to("cuda:0")
+    return x[off:], y[off:], xd[off:], yd[off:]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("dtype,guard,off", [(np.float64, 0, 0), (np.float64, 1, 0),
+                                             (np.float64, 0, 1), (np.float32, 0, 0),
+                                             (np.float32, 0, 1), (np.float32, 1, 0)])
+def test_lengths(h, n, dtype, guard, off):
+    x, y, xd, yd = _pair(n, 71 + n % 97, dtype, off)
+    f64 = dtype == np.float64
+    opt = [0, 0, 0, 0, guard]
+    for tol in (1e-3, 1e-8):
+        o = (oracle.qdot if f64 else oracle.qdot_f32)(x, y, tol, opt=opt)
+        call = h.qdot if f64 else h.qdot_f32
+        for r in (call(xd, yd, tol, opt), call(xd, yd, tol, opt)):
+            for k in FIELDS:
+                assert r[k] == o[k], (k, r[k], o[k])
+            assert abs(r["value"] - o["value"]) <= 1e-13 * oracle.abs_dot(
+                x.astype(np.float64), y.astype(np.float64))
+
+
+@pytest.mark.parametrize("n", [700, 3000, 30000, 200000, 600000])
+@pytest.mark.parametrize("opt", [[0, 0, 0, 0, 0], [1, 1, 0, 0, 0], [0, 0, 1, 0, 0],
+                                 [0, 0, 0, 0, 1], [0, 1, 1, 0, 1]])
+def test_same_as_four_kernel_chain(h, n, opt):
+    """Every form of the options, on cancelling sums (which the guaranteed
+    mode selects again): the classes, counts and leaves are the chain's, the
+    compensated FP64 sums differ by their error terms' rounding at most."""
+    import torch
+    x, y = workloads.cancelling_pair(n, n, 3e-4)
+    xd, yd = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(y).to("cuda:0")
+    with q.Qdot(0) as other:
+        other.set_tune(-1, 2, 1, 2, 1, block_threads=128)
+        for tol in (1e-2, 1e-5):
+            r, c = h.qdot(xd, yd, tol, opt), other.qdot(xd, yd, tol, opt)
+            for k in FIELDS:
+                assert r[k] == c[k], (k, r[k], c[k])
+            assert r["bound_rel"] == c["bound_rel"]
+            assert abs(r["value"] - c["value"]) <= 4e-16 * oracle.abs_dot(x, y)
+
+
+@pytest.mark.parametrize("n", [1000, 4000, 100000])
+def test_error_results_leave_the_workspace_clean(h, n):
+    import torch
+    x, y, xd, yd = _pair(n, 5, np.float64, 0)
+    bad = xd.clone()
+    bad[n - 1] = float("inf")
+    ref = h.qdot(xd, yd, 1e-6)
+    e = h.qdot(bad, yd, 1e-6)
+    assert e["status"] == q.E_NONFINITE and np.isnan(e["value"]) and e["count"] == [0] * 4
+    z = h.qdot(torch.zeros_like(xd), yd, 1e-6, [0, 0, 0, 0, 1])
+    assert z["value"] == 0.0 and z["n_zero"] == n and z["flags"] & q.F_GUARANTEED
+    assert h.qdot(xd, yd, 1e-6) == ref
