@@ -1068,6 +1068,8 @@ hipError_t launch_qdot_pair(const Launch &La, const Launch &Lb, const double *x,
                             const double *w, int64_t n, double tol, const qdot_options &o,
                             qdot_result *out_a, qdot_result *out_b, int nscan_pre)
 {
+    if (nscan_pre < 0 && fused_ok(La, n, o))
+        return launch_fused_pair(La, Lb, x, w, n, tol, o, out_a, out_b);
     const bool vec = ((((uintptr_t)x) | ((uintptr_t)w)) & 15) == 0;
     return vec ? launch_pair_v<true>(La, Lb, x, w, n, tol, o, out_a, out_b, nscan_pre)
                : launch_pair_v<false>(La, Lb, x, w, n, tol, o, out_a, out_b, nscan_pre);

@@ -63,6 +63,11 @@ hipError_t launch_fused(const Launch &L, const double *x, const double *y, int64
 hipError_t launch_fused(const Launch &L, const float *x, const float *y, int64_t n, double tol,
                         const qdot_options &o, qdot_result *out);
 
+// The power method's pair of launch_qdot_pair likewise.
+hipError_t launch_fused_pair(const Launch &La, const Launch &Lb, const double *x,
+                             const double *w, int64_t n, double tol, const qdot_options &o,
+                             qdot_result *out_a, qdot_result *out_b);
+
 // Enqueue the plain FP64 dot; *out receives sum x_i y_i.
 hipError_t launch_dot64(const Launch &L, const double *x, const double *y, int64_t n,
                         double *out);

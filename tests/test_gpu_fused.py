@@ -87,3 +87,25 @@ def test_error_results_leave_the_workspace_clean(h, n):
     z = h.qdot(torch.zeros_like(xd), yd, 1e-6, [0, 0, 0, 0, 1])
     assert z["value"] == 0.0 and z["n_zero"] == n and z["flags"] & q.F_GUARANTEED
     assert h.qdot(xd, yd, 1e-6) == ref
+
+
+@pytest.mark.parametrize("m", [1, 5, 16, 64, 82])
+@pytest.mark.parametrize("opt", [[0, 0, 0, 0, 0], [1, 0, 1, 0, 0], [0, 0, 0, 0, 1]])
+def test_power_pair(m, opt):
+    """The pair of inner products of a power step in two launches, against
+    the four-kernel chain of the other launch shapes: every field but the
+    compensated sums' last bits."""
+    import torch
+    A = q.Csr(*workloads.laplacian3d_csr(m))
+    x0 = torch.from_numpy(workloads.unit_vector(A.n, m + 2)).to("cuda:0")
+    res = []
+    for nt in (256, 128):
+        with q.Qdot(0) as hh:
+            hh.set_tune(-1, 2, 1, 2, 1, block_threads=nt)
+            res.append(hh.power(A, x0.clone(), 6, 1e-6, 1, opt=opt, results=True))
+    for a, b in zip(*(r["results"] for r in res)):
+        for k in FIELDS:
+            assert a[k] == b[k], (k, a[k], b[k])
+        # products of one sign (w . w) or nearly cancelling ones (x . w): the
+        # sum of |x_i w_i| is at most sqrt(x.x) sqrt(w.w) <= 12
+        assert abs(a["value"] - b["value"]) <= 12 * 1e-13
