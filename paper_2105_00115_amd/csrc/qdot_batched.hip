@@ -6,7 +6,8 @@
 //         component groups c, c + nc, c + 2 nc, ... so that the blocks on
 //         one instance read neighbouring addresses at any moment,
 //   SMALL runs of whole small instances (n <= chunk each), grouped so
-//         that sum(n + SMALL_COST0) stays within SMALL_GROUP per item (the
+//         that sum(n + SMALL_COST0) stays within SMALL_GROUP per item, or
+//         within the resident blocks' share when that is less (the
 //         fixed term stands for the latency chain of one instance), each
 //         instance done start to finish by one block with a block-local
 //         cutoff,
@@ -30,7 +31,7 @@
 #include <cstring>
 #include <numeric>
 
-#include "qdot_blocks.hpp"
+#include "qdot_select.hpp"
 #include "qdot_cg.hpp"
 #include "qdot_handle.hpp"
 
@@ -274,6 +275,73 @@ __device__ __forceinline__ void p1_onepass(const double *xi, const double *yi, i
     }
 }
 
+// One small instance, two-pass, start to finish by one block: the counts in
+// LD.h (zero before and after), the selection and the result of
+// qdot_select.hpp.  GUARD: certified, or selected and swept again.  It is a
+// chain of latencies: 256 instances of 1e2 to 1e4 components, one per block,
+// take 22.7 us per launch, against 83 in runs of SMALL_GROUP with the
+// selection and reductions of the four-kernel chain.
+template <bool GUARD>
+__device__ __forceinline__ void small_instance(const double *xi, const double *yi, int64_t n,
+                                               bool vec, const SelArgs &a, CgLds &LD,
+                                               SelLds<BLOCK> &S, qdot_result *o)
+{
+    constexpr int K = (FQ + BLOCK - 1) / BLOCK;
+    const int tid = threadIdx.x;
+    unsigned int *h = LD.h;
+    uint4 *h4 = reinterpret_cast<uint4 *>(h);
+    select_begin(S);
+    unsigned int sg = 0;
+    auto count = [&](const double *xv, const double *yv, int64_t, int lim) {
+        count4(xv, yv, lim, a.key_mode, h, sg);
+    };
+    if (vec) stream_strided<true, SU>(xi, yi, 0, GROUP, n, count);
+    else stream_strided<false, SU>(xi, yi, 0, GROUP, n, count);
+    count_signs(sg, h);
+    __syncthreads();
+    {
+        uint4 v[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int q = k * BLOCK + tid;
+            v[k] = q < FQ ? h4[q] : make_uint4(0u, 0u, 0u, 0u);
+        }
+        find_window<BLOCK, K>(v, S);
+    }
+    __syncthreads();
+    const Sel s = select_classes<BLOCK>(h, a, S, LD.lut);
+    auto sweep = [&](int e_max, int c32) {
+        Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+        accumulate_range(xi, yi, 0, GROUP, n, vec, a.key_mode, LD.lut, e_max, c32, acc);
+        block_reduce3_waves<BLOCK, false>(acc, LD.red);
+        __syncthreads();
+    };
+    select_count<BLOCK>(h, s, a, S);
+    if (s.live()) sweep(s.e_max, s.c32);
+    else __syncthreads();
+    finish_result<BLOCK>(s, a, n, S, LD.red, LD.res);
+    if constexpr (GUARD) {
+        const int lo = s.n_bins ? s.e_min - KMIN : W, hi = s.n_bins ? s.e_max - KMIN : -1;
+        auto get = [&](int j) { return (unsigned long long)h[j]; };
+        auto put = [&](int j, int c) { LD.lut[j] = (unsigned char)c; };
+        block_guard<BLOCK>(lo, hi, s.n_zero, s.signs, n, a.tol, a.score_mode, a.nonstrict, get,
+                           put, LD.lut, S.sum, LD.res, [&](const CutParams &p, int flags) {
+                               sweep(p.e_max, p.c32);
+                               if (tid != 0) return 0.0;
+                               Acc b[3];
+                               for (int q = 0; q < 3; q++) {
+                                   b[q] = LD.red[q][0];
+                                   for (int w = 1; w < BLOCK / 64; w++)
+                                       b[q] = acc_merge(b[q], LD.red[q][w]);
+                               }
+                               return combine_value(b, p.e_max, p.c32, flags, &LD.res);
+                           });
+        __syncthreads();
+    }
+    put_result(o, LD.res);
+    for (int i = tid; i < FQ; i += BLOCK) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 __global__ __launch_bounds__(BLOCK) void k_batch_init(BLarge *large, int n_large,
                                                       unsigned char *lut)
 {
@@ -327,6 +395,7 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
     constexpr int accum_mode = AM;
     __shared__ CgLds LD;
     __shared__ S1Lds S1;
+    __shared__ SelLds<BLOCK> SL;
     unsigned int *h = LD.h;
     unsigned char *lut = LD.lut;
     auto &red = LD.red;
@@ -336,7 +405,7 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
     __shared__ int4 s_prm2;
     const int tid = threadIdx.x;
 
-    for (int i = tid; i < W + 1; i += BLOCK) h[i] = 0;
+    for (int i = tid; i < 4 * FQ; i += BLOCK) h[i] = 0;
     for (int i = W + tid; i < W_LUT; i += BLOCK) lut[i] = (unsigned char)QDOT_PERF;
     __syncthreads();
 
@@ -364,10 +433,9 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
             const double *yi = y + off;
             const bool vec = ((((uintptr_t)xi) | ((uintptr_t)yi)) & 15) == 0;
             const double tol = tols[inst];
-            unsigned int nz = 0, bad = 0, sg = 0;
-            int top = -1, depth = 0;
-            if (accum_mode == 1) {
-                depth = s1_window_depth(n, tol, score_mode);
+            if constexpr (accum_mode == 1) {
+                unsigned int nz = 0, bad = 0;
+                const int depth = s1_window_depth(n, tol, score_mode);
                 if (depth < 0) {  // kept bins could lie beyond the window
                     if (tid == 0) write_invalid(out + inst);
                     __syncthreads();
@@ -380,64 +448,32 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
                     s1_stream<true, SU>(xi, yi, 0, GROUP, n, key_mode, depth, h, S1, run, nz, bad);
                 else
                     s1_stream<false, SU>(xi, yi, 0, GROUP, n, key_mode, depth, h, S1, run, nz, bad);
-                top = run.top;
-            } else {
-                scan_into(xi, yi, 0, GROUP, n, vec, key_mode, h, nz, bad, sg);
-            }
-            __syncthreads();
-            int lo = W, hi = -1;
-            for (int j = tid; j < W; j += BLOCK)
-                if (h[j]) {
-                    lo = min(lo, j);
-                    hi = max(hi, j);
-                }
-            unsigned int bs = (bad ? 1u : 0u) | (sg << 1);
-            block_reduce_range(lo, hi, nz, bs, scratch);
-            bad = bs & 1u;
-            sg = bs >> 1;
-            auto get = [&](int j) { return (unsigned long long)h[j]; };
-            auto put = [&](int j, int c) { lut[j] = (unsigned char)c; };
-            // the guaranteed mode reads the counts again after the sweep
-            auto clear = [&](int j) {
-                if (!GUARD) h[j] = 0u;
-            };
-            const CutParams p = block_cutoff<BLOCK>(lo, hi, nz, bad, n, tol, score_mode,
-                                                    nonstrict, get, put, clear,
-                                                    GUARD ? &s_res : out + inst, nullptr);
-            if (tid == 0) h[W] = 0u;
-            __syncthreads();
-            if (accum_mode == 1) {
+                const int top = run.top;
+                __syncthreads();
+                int lo = W, hi = -1;
+                for (int j = tid; j < W; j += BLOCK)
+                    if (h[j]) {
+                        lo = min(lo, j);
+                        hi = max(hi, j);
+                    }
+                block_reduce_range(lo, hi, nz, bad, scratch);
+                auto get = [&](int j) { return (unsigned long long)h[j]; };
+                auto put = [&](int j, int c) { lut[j] = (unsigned char)c; };
+                auto clear = [&](int j) { h[j] = 0u; };
+                const CutParams p = block_cutoff<BLOCK>(lo, hi, nz, bad, n, tol, score_mode,
+                                                        nonstrict, get, put, clear, out + inst,
+                                                        nullptr);
+                if (tid == 0) h[W] = 0u;
+                __syncthreads();
                 // one pass: each kept bin's class sum straight from the window
                 if (!p.skip)
                     s1_pick(p.e_max, max(lo, top - depth + 1), p.flags, lut,
                             [&](int bin, int q) { return S1.win[bin & (S1_WIN - 1)][q]; }, red,
                             out + inst);
-            } else if constexpr (GUARD) {
-                // the whole instance is swept by this block: first sweep,
-                // certification, and a second sweep after a reselection
-                auto sweep = [&](const CutParams &cp, int flags) {
-                    Acc a[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-                    accumulate_range(xi, yi, 0, GROUP, n, vec, key_mode, lut, cp.e_max, cp.c32, a);
-                    block_reduce3<BLOCK>(a, red);
-                    return tid == 0 ? combine_value(a, cp.e_max, cp.c32, flags, &s_res) : 0.0;
-                };
-                __shared__ double s_first;
-                if (tid == 0) s_first = 0.0;
-                __syncthreads();
-                if (!p.skip) {
-                    const double s0 = sweep(p, p.flags);
-                    if (tid == 0) s_first = s0;
-                }
-                __syncthreads();
-                block_guard<BLOCK>(lo, hi, nz, sg, n, tol, score_mode, nonstrict, get, put, lut, s_first,
-                            s_res, sweep);
-                put_result(out + inst, s_res);
-                for (int j = lo + tid; j <= hi; j += BLOCK) h[j] = 0u;
-            } else if (!p.skip) {
-                Acc a[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-                accumulate_range(xi, yi, 0, GROUP, n, vec, key_mode, lut, p.e_max, p.c32, a);
-                block_reduce3<BLOCK>(a, red);
-                if (tid == 0) combine_value(a, p.e_max, p.c32, p.flags, out + inst);
+            } else {
+                small_instance<GUARD>(xi, yi, n, vec,
+                                      SelArgs{key_mode, score_mode, nonstrict, 0, tol}, LD, SL,
+                                      out + inst);
             }
             __syncthreads();
           }
@@ -741,11 +777,18 @@ static int32_t build_plan(qdot_handle *h, const int64_t *host_offsets, int32_t B
         slot += (int)nc;
     }
     std::vector<int> small_list(small.begin(), small.end());
+    // runs short enough that every resident block gets one: a few instances
+    // are spread over the chip rather than queued in full runs (256 instances
+    // of 1e2 to 1e4 components in runs of SMALL_GROUP kept 45 blocks busy)
+    int64_t small_cost = 0;
+    for (int j : small) small_cost += len(j) + SMALL_COST0;
+    const int64_t resident = (int64_t)h->batch_blocks_per_cu * h->num_cus;
+    const int64_t budget = std::min(SMALL_GROUP, small_cost / resident);
     for (size_t s0 = 0; s0 < small_list.size();) {
         size_t s1 = s0;
         int64_t cost = 0;
         while (s1 < small_list.size() &&
-               (s1 == s0 || cost + len(small_list[s1]) + SMALL_COST0 <= SMALL_GROUP)) {
+               (s1 == s0 || cost + len(small_list[s1]) + SMALL_COST0 <= budget)) {
             cost += len(small_list[s1]) + SMALL_COST0;
             s1++;
         }

@@ -170,7 +170,9 @@ struct DotOut {
 
 // Shared-memory workspace of one block (CG and batched kernels).
 struct CgLds {
-    unsigned int h[W + 1];
+    // the key slots, the spare slot W, and three more words (the batched
+    // kernel counts signs and non-finite products there, qdot_select.hpp)
+    alignas(16) unsigned int h[4 * FQ];
     unsigned char lut[W_LUT];
     Acc red[3][BLOCK / 64];
     int4 scratch[BLOCK / 64];

@@ -109,3 +109,30 @@ def test_power_pair(m, opt):
         # products of one sign (w . w) or nearly cancelling ones (x . w): the
         # sum of |x_i w_i| is at most sqrt(x.x) sqrt(w.w) <= 12
         assert abs(a["value"] - b["value"]) <= 12 * 1e-13
+
+
+@pytest.mark.parametrize("count", [1, 3, 767, 769, 1600])
+@pytest.mark.parametrize("guard", [0, 1])
+def test_small_instances_spread_over_blocks(h, count, guard):
+    """Runs of small instances at one instance per block, at one more than
+    the resident blocks and at two per block, with lengths around a chunk and
+    a group: each instance against the oracle."""
+    import torch
+    lens = [(0, 1, 63, 1024, 1025, 2047, 2048, 2049, 300)[i % 9] for i in range(count)]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(off[-1])
+    x, y = workloads.log_uniform_pair(n + 1, 40 + count)
+    x, y = x[:n], y[:n]
+    if n:
+        x[n // 2] = 0.0
+    tols = [(1e-4, 1e-6, 1e-8)[i % 3] for i in range(count)]
+    xd, yd = torch.from_numpy(x).to("cuda:0"), torch.from_numpy(y).to("cuda:0")
+    opt = [0, 0, 0, 0, guard]
+    for _ in range(2):
+        res = h.batched(xd, yd, off, tols, opt)
+        for j, r in enumerate(res):
+            a, b = x[off[j]:off[j + 1]], y[off[j]:off[j + 1]]
+            o = oracle.qdot(a, b, tols[j], opt=opt)
+            for k in ("count", "n_zero", "e_min", "e_max", "n_bins", "t", "flags", "status"):
+                assert r[k] == o[k], (j, k, r[k], o[k])
+            assert abs(r["value"] - o["value"]) <= 1e-13 * oracle.abs_dot(a, b)
