@@ -457,7 +457,9 @@ typedef struct qdot_solver_tune {
                                   a multiple of 2048 */
     int32_t cg_rows_per_block; /* a batched CG system of n rows gets
                                   ceil(n / this) gang blocks, >= 1024 ... */
-    int32_t cg_gang_max;       /* ... and at most this many, 1..512 */
+    int32_t cg_gang_max;       /* ... and at most this many, 1..512 (both:
+                                  unless that leaves resident blocks idle,
+                                  which the gangs then share) */
     int32_t spmv_blocks_per_cu; /* SpMV grid (qdot_spmv_async, the power
                                    method), blocks per CU, 1..16 */
     int32_t cg_blocks_per_cu;  /* qdot_cg: gang blocks per CU, 1..2 (capped by

@@ -136,3 +136,26 @@ def test_small_instances_spread_over_blocks(h, count, guard):
             for k in ("count", "n_zero", "e_min", "e_max", "n_bins", "t", "flags", "status"):
                 assert r[k] == o[k], (j, k, r[k], o[k])
             assert abs(r["value"] - o["value"]) <= 1e-13 * oracle.abs_dot(a, b)
+
+
+@pytest.mark.parametrize("sides", [[1], [33], [32, 40, 200], [32] * 40 + [181], [100] * 70,
+                                   [300, 300, 299]])
+def test_gangs_shared_out(h, sides):
+    """Batches whose gangs would leave resident blocks idle get larger ones:
+    rows split at every chunk, a gang of one block, gangs at the bound of 64,
+    and a batch that fills the chip at the tuned shape.  Each system takes the
+    iteration count and the solution of the single-system solve, whose gang
+    has another shape (every inner product is the same but for FP64 error
+    terms, so 40 iterations stay far above the tolerance's 1e-9)."""
+    import torch
+    systems = []
+    for i, m in enumerate(sides):
+        A = q.Csr(*workloads.poisson2d_csr(m))
+        b = torch.from_numpy(workloads.normal_vector(A.n, 60 + i)).to("cuda:0")
+        systems.append((A, b, torch.zeros_like(b), 1e-8, 1e-8, 40, 1))
+    res = h.cg_batched(systems)
+    for (A, b, x, *_), r in list(zip(systems, res))[::max(1, len(sides) // 4)]:
+        xs = torch.zeros_like(b)
+        one = h.cg(A, b, xs, 1e-8, 1e-8, 40, 1)
+        assert (r["iters"], r["status"]) == (one["iters"], one["status"])
+        assert float((x - xs).norm()) <= 1e-9 * float(xs.norm())
