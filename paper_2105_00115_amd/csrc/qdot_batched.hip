@@ -44,6 +44,9 @@ constexpr int64_t SMALL_GROUP = 65536; // cost budget of one item of small insta
 constexpr int SU = 2;                 // CHUNK groups in flight per thread
 constexpr int64_t GROUP = (int64_t)SU * CHUNK;
 constexpr int MAX_PLANS = 8;
+// entries of a gang block's rows kept in LDS (two blocks per CU; the one-pass
+// window of the instances leaves less room)
+constexpr int BATCH_LE = 3840, BATCH_LE_ONEPASS = 2048;
 // A CG system of n rows gets a gang of ceil(n / batch_cg_rows) blocks, at
 // most batch_cg_gang_max (handle fields; defaults 16384 and 16), or more when
 // the batch would leave resident blocks idle (gang_shape).
@@ -284,11 +287,12 @@ __device__ __forceinline__ void p1_onepass(const double *xi, const double *yi, i
 // selection and reductions of the four-kernel chain.
 template <bool GUARD>
 __device__ __forceinline__ void small_instance(const double *xi, const double *yi, int64_t n,
-                                               bool vec, const SelArgs &a, CgLds &LD,
-                                               SelLds<BLOCK> &S, qdot_result *o)
+                                               bool vec, const SelArgs &a, CgLdsT<BLOCK> &LD,
+                                               qdot_result *o)
 {
     constexpr int K = (FQ + BLOCK - 1) / BLOCK;
     const int tid = threadIdx.x;
+    SelLds<BLOCK> &S = LD.sel;
     unsigned int *h = LD.h;
     uint4 *h4 = reinterpret_cast<uint4 *>(h);
     select_begin(S);
@@ -357,7 +361,6 @@ __global__ __launch_bounds__(BLOCK) void k_batch_gangs_init(Gang *gangs, int S)
 {
     if (blockIdx.x >= (unsigned)S) return;
     gang_reset(gangs + blockIdx.x);
-    if (threadIdx.x == 0) gangs[blockIdx.x].bar_gen = 0;
 }
 
 // Re-arms the gangs of a plan whose previous launch aborted (a bounded wait
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(BLOCK) void k_gang_rearm(Gang *gangs, int S)
 // kernel, 168 VGPRs (three per CU) for the one-pass one, against two per CU
 // for the kernel that holds every path.
 template <bool GUARD, bool CG, int AM>
-__global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_batch(const double *__restrict__ x,
+__global__ __launch_bounds__(BLOCK, GUARD ? 1 : CG ? 2 : (AM ? 3 : 4)) void k_batch(const double *__restrict__ x,
                                                  const double *__restrict__ y,
                                                  const int64_t *__restrict__ offsets,
                                                  const double *__restrict__ tols,
@@ -394,9 +397,8 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
                                                  int score_mode, int nonstrict)
 {
     constexpr int accum_mode = AM;
-    __shared__ CgLds LD;
+    __shared__ CgLdsT<BLOCK> LD;
     __shared__ S1Lds S1;
-    __shared__ SelLds<BLOCK> SL;
     unsigned int *h = LD.h;
     unsigned char *lut = LD.lut;
     auto &red = LD.red;
@@ -417,13 +419,17 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
         __syncthreads();
         if (it >= n_items) break;
         const BItem I = items[it];
-        if (CG && I.type == IT_CG) {
-            // one block of a CG gang: its other blocks hold the neighbouring
-            // tickets, so they are taken by blocks that are running
-            cg_solve<GUARD>(sys[I.inst], gangs + I.inst, I.large, I.slot, key_mode, score_mode,
-                            nonstrict, LD, cg_out + I.inst);
-            __syncthreads();
-            continue;
+        if constexpr (CG) {
+            if (I.type == IT_CG) {
+                // one block of a CG gang: its other blocks hold the neighbouring
+                // tickets, so they are taken by blocks that are running
+                constexpr int LE = AM ? BATCH_LE_ONEPASS : BATCH_LE;
+                __shared__ MatLds<BLOCK, LE> M;
+                cg_solve<GUARD, BLOCK, LE>(sys[I.inst], gangs + I.inst, I.large, I.slot, key_mode,
+                                           score_mode, nonstrict, LD, M, cg_out + I.inst);
+                __syncthreads();
+                continue;
+            }
         }
         if (I.type == IT_SMALL) {
           for (int sj = 0; sj < I.large; sj++) {
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(BLOCK, (CG || GUARD) ? 1 : (AM ? 3 : 4)) void k_bat
                             out + inst);
             } else {
                 small_instance<GUARD>(xi, yi, n, vec,
-                                      SelArgs{key_mode, score_mode, nonstrict, 0, tol}, LD, SL,
+                                      SelArgs{key_mode, score_mode, nonstrict, 0, tol}, LD,
                                       out + inst);
             }
             __syncthreads();

@@ -11,8 +11,17 @@ namespace qd {
 
 // GUARD: guard_mode 1; ACC1: accum_mode 1 (tab: the gang's one-pass
 // tables, zero on entry and on exit).
-template <bool GUARD, bool ACC1>
-__global__ __launch_bounds__(BLOCK) void k_cg_gangs(const CgSys *__restrict__ sys,
+// The two-pass gang: one block of 1024 threads per CU, so that few blocks meet
+// at a barrier and the block's slice has the CU's whole LDS (CG_ENTRIES of its
+// matrix entries stay there, qdot_cg.hpp).  Poisson 1024^2, per iteration:
+// 53.7 us, 56.3 with 512 threads.  The guaranteed and the one-pass mode hold
+// too many registers for it and run two blocks of BLOCK threads per CU.
+constexpr int CG_THREADS = 1024;
+constexpr int CG_ENTRIES = 10240;
+constexpr int CG_ENTRIES_SMALL = 3840, CG_ENTRIES_ONEPASS = 2048;
+
+template <bool GUARD, bool ACC1, int NT>
+__global__ __launch_bounds__(NT, NT > BLOCK ? 4 : 2) void k_cg_gangs(const CgSys *__restrict__ sys,
                                                     const int *__restrict__ gang_sys,
                                                     const int *__restrict__ gang_sys_off,
                                                     Gang *__restrict__ gangs, int G,
@@ -20,16 +29,19 @@ __global__ __launch_bounds__(BLOCK) void k_cg_gangs(const CgSys *__restrict__ sy
                                                     int key_mode, int score_mode, int nonstrict,
                                                     double *__restrict__ tab)
 {
-    __shared__ CgLds L;
-    for (int i = threadIdx.x; i < W + 1; i += BLOCK) L.h[i] = 0u;
-    for (int i = W + threadIdx.x; i < W_LUT; i += BLOCK) L.lut[i] = (unsigned char)QDOT_PERF;
+    constexpr int LE = NT > BLOCK ? CG_ENTRIES : ACC1 ? CG_ENTRIES_ONEPASS : CG_ENTRIES_SMALL;
+    __shared__ CgLdsT<NT> L;
+    __shared__ MatLds<NT, LE> M;
+    static_assert(sizeof L + sizeof M + (ACC1 ? sizeof(S1Lds) : 0) < 160 * 1024 / (NT > BLOCK ? 1 : 2), "LDS");
+    for (int i = threadIdx.x; i < 4 * FQ; i += NT) L.h[i] = 0u;
+    for (int i = W + threadIdx.x; i < W_LUT; i += NT) L.lut[i] = (unsigned char)QDOT_PERF;
     __syncthreads();
     const int g = blockIdx.x / G, gb = blockIdx.x % G;
     Gang *gg = gangs + g;
     auto run = [&](S1Lds *S1) {
         for (int s = gang_sys_off[g]; s < gang_sys_off[g + 1]; s++) {
-            cg_solve<GUARD, ACC1>(sys[gang_sys[s]], gg, G, gb, key_mode, score_mode, nonstrict,
-                                  L, res + gang_sys[s], S1, tab);
+            cg_solve<GUARD, NT, LE, ACC1>(sys[gang_sys[s]], gg, G, gb, key_mode, score_mode,
+                                          nonstrict, L, M, res + gang_sys[s], S1, tab);
             if (__hip_atomic_load(&gg->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
         }
     };
@@ -46,7 +58,6 @@ __global__ void k_gang_init(Gang *gangs, int n)
     const int g = blockIdx.x;
     if (g >= n) return;
     gang_reset(gangs + g);
-    if (threadIdx.x == 0) gangs[g].bar_gen = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -145,20 +156,14 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
     if ((st = ensure_cg_buffers(h, 1, 1)) != QDOT_OK) return st;
     CgDev *d = (CgDev *)h->cg;
     hipStream_t s = (hipStream_t)stream;
-    // one gang: up to two blocks per CU (as many as are resident together),
-    // at least CHUNK rows per block.  Two blocks per CU keep twice the
-    // SpMV's gathers in flight; measured on Poisson 1024^2 the iteration
-    // took 87 us instead of 92 with qdot and 49 instead of 59 with the FP64
-    // dot.
+    // one gang, at least CHUNK rows per block: one block of CG_THREADS per CU,
+    // or up to two of BLOCK threads
+    const void *kernel = acc1           ? (const void *)k_cg_gangs<false, true, BLOCK>
+                         : o.guard_mode ? (const void *)k_cg_gangs<true, false, BLOCK>
+                                        : (const void *)k_cg_gangs<false, false, CG_THREADS>;
+    const int nt = acc1 || o.guard_mode ? BLOCK : CG_THREADS;
     int per_cu = 0;
-    hipError_t oe =
-        acc1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cg_gangs<false, true>,
-                                                           BLOCK, 0)
-        : o.guard_mode
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cg_gangs<true, false>, BLOCK,
-                                                           0)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cg_gangs<false, false>,
-                                                           BLOCK, 0);
+    hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, nt, 0);
     if (oe != hipSuccess) return hip_fail(h, oe, "occupancy query");
     if (per_cu < 1) return fail(h, QDOT_E_DEVICE, "the CG kernel cannot be resident");
     const int cap = std::min(MAX_GANG, std::min(per_cu, h->cg_blocks_per_cu) * h->num_cus);
@@ -192,17 +197,17 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_gang_init, dim3(1), dim3(BLOCK), 0, s, d->gangs, 1);
         if (acc1)
-            hipLaunchKernelGGL((k_cg_gangs<false, true>), dim3(G), dim3(BLOCK), 0, s, d->sys,
-                               d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
+            hipLaunchKernelGGL((k_cg_gangs<false, true, BLOCK>), dim3(G), dim3(BLOCK), 0, s,
+                               d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
                                o.score_mode, o.boundary_mode, d->s1tab);
         else if (o.guard_mode)
-            hipLaunchKernelGGL((k_cg_gangs<true, false>), dim3(G), dim3(BLOCK), 0, s, d->sys,
-                               d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
+            hipLaunchKernelGGL((k_cg_gangs<true, false, BLOCK>), dim3(G), dim3(BLOCK), 0, s,
+                               d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
                                o.score_mode, o.boundary_mode, (double *)nullptr);
         else
-            hipLaunchKernelGGL((k_cg_gangs<false, false>), dim3(G), dim3(BLOCK), 0, s, d->sys,
-                               d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
-                               o.score_mode, o.boundary_mode, (double *)nullptr);
+            hipLaunchKernelGGL((k_cg_gangs<false, false, CG_THREADS>), dim3(G), dim3(CG_THREADS),
+                               0, s, d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res,
+                               o.key_mode, o.score_mode, o.boundary_mode, (double *)nullptr);
         e = hipGetLastError();
     }
     if (e == hipSuccess)

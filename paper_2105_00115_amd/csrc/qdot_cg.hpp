@@ -1,32 +1,41 @@
 // Device side of conjugate gradient (Alg. 4) run by a gang of blocks inside
 // one launch; used by the single-system CG launch and by the batched launch.
 //
-// A gang of G blocks solves one system; block b of the gang owns a
-// contiguous slice of rows and every vector update, SpMV row and qdot pass
-// on that slice.  Gang barriers (an arrival counter and a generation word)
-// separate the steps that need data from other slices:
+// A gang of G blocks of NT threads solves one system; block b of the gang
+// owns a contiguous slice of rows and every vector update, SpMV row and qdot
+// pass on that slice.  Gang barriers separate the steps that need data from
+// other slices:
 //   before the SpMV (p complete), after a qdot's pass 1 (histogram merged),
 //   after its pass 2 (partials written),
 // five per iteration (one more for an inner product that the guaranteed
-// mode sums again; one fewer per inner product in the one-pass mode).  The
-// whole-gang reductions (the blocks' pass-1 records and histogram copies at
-// the first barrier of a qdot, its partials at the second) are done once,
-// by the last block to arrive, before it releases the others; that block
-// also clears the histogram copies.  Every block then computes the cutoff
-// itself from the same merged histogram and finishes the combine from the
-// same published words, so every block holds bit-identical scalars (alpha,
-// beta, c) and takes the same branches: no decision is broadcast.  Two
-// buffers alternate between consecutive qdots.
+// mode sums again; one fewer per inner product in the one-pass mode).
+//
+// An iteration is a chain of latencies: each barrier costs several round
+// trips to the memory that all XCDs share (0.7 to 1 us each), so they are kept
+// few.  The counters of a barrier only ever count up (no resets, and a block
+// knows the generation it waits for without reading it); blocks arrive in
+// groups, and poll their group's own copy of the release word.  The
+// histograms of a group are added to the gang's by the group's last block
+// while the other groups still arrive; every block then reads the merged
+// counts in one round trip, whole, and selects the classes itself.  The
+// partials are combined by the last block to arrive, which releases the
+// others with the value itself: the word they poll is the inner product.
+// Poisson 1024^2, per iteration with the two-pass qdot: 87 us with counters
+// reset at each barrier, a whole-gang merge and combine by the last block and
+// 512 blocks of 256 threads; 64 us this way; 53.7 us with the matrix's
+// resident rows (below).  With the FP64 dot: 48 -> 32.8 us.
+// Every block holds bit-identical scalars (alpha, beta, c) and takes the same
+// branches: no decision is broadcast.  Two buffers alternate between
+// consecutive qdots.
 //
 // Every wait is bounded: a barrier that does not complete within the spin
 // limit raises the gang's abort flag, every block leaves, and the call
 // reports QDOT_E_DEVICE.  The launches size their grids so that all blocks
-// of a gang are resident together (the single-system launch: up to two
-// blocks per CU when the kernel's occupancy allows it).
+// of a gang are resident together.
 #pragma once
 #include <cmath>
 
-#include "qdot_blocks.hpp"
+#include "qdot_select.hpp"
 
 namespace qd {
 
@@ -46,120 +55,190 @@ struct CgSys {
 };
 
 constexpr int MAX_GANG = 512;
-// block gb of a gang merges its histogram into copy gb % GANG_HIST_COPIES:
-// the merge atomics of one slot then queue 8 ways instead of G deep, and
-// every block waits for its own atomics before it arrives at the barrier
-constexpr int GANG_HIST_COPIES = 8;
+constexpr int BAR_GROUPS = 8;     // groups of a large gang: block gb in group gb mod 8
+constexpr int BAR_ONE_LEVEL = 64; // gangs up to this size are one group
 
-struct GangQ {  // per gang and qdot buffer
-    unsigned int hist[GANG_HIST_COPIES][W];
-    // per block: live slot range, zero count, and non-finite flag (bit 0)
-    // with the signs of the nonzero products (bit 1 negative, bit 2
-    // positive); written by every block for every inner product, so never
-    // cleared
-    int4 rec[MAX_GANG];
-    // published by the last block to arrive at the merge barrier: the
-    // reduced records (lo, hi, zeros, flags) and the summed copies over
-    // [lo, hi] (the copies are cleared by the same block)
-    int4 sum;
-    unsigned int hm[W];
+struct GangLine {  // a word, or two, on a 128-byte line of their own
+    unsigned int v;
+    unsigned int pad;
+    unsigned long long w;
+    unsigned int fill[28];
 };
 
-constexpr int BAR_GROUPS = 8;    // first level of the barrier of a large gang
-constexpr int BAR_TWO_LEVEL = 64; // gangs larger than this use two levels
+struct GangQ {  // per gang and qdot buffer; zero between its uses
+    // a large gang's groups: the counts of one group's blocks each
+    uint4 hist[BAR_GROUPS][FQ];
+    // the gang's counts (slots, and the four counts behind them)
+    uint4 hm[FQ];
+};
+
+// The word in place of a value that is not there yet: a NaN that no sum has.
+constexpr unsigned long long NO_VALUE = 0x7ff4dead00c0ffeeull;
 
 struct Gang {
-    unsigned int bar_count;
-    unsigned int bar_gen;
     unsigned int abort;
-    unsigned int pad;
+    unsigned int pad[31];
+    GangLine sub[BAR_GROUPS];     // .v: arrivals of a group's blocks
+    GangLine top;                 // .v: arrivals of the groups
+    GangLine gen[BAR_GROUPS];     // .v: the group's copy of the generation
+    GangLine val[2][BAR_GROUPS];  // .w: the group's copy of dot buffer k's value
     GangQ qb[2];
     double partials[2][MAX_GANG * 6];
     // partials[k] combined in block order by the last block to arrive
     double pfin[2][6];
-    // one-pass mode: the result of buffer k's qdot, published by the last
-    // block to arrive
+    // one-pass mode: per block the live slot range, zero count and non-finite
+    // flag, and the result of buffer k's qdot, published by the last block to
+    // arrive
+    int4 rec[2][MAX_GANG];
     qdot_result res[2];
-    unsigned int bar_sub[BAR_GROUPS][32];  // group counters, one 128-byte line each
 };
 
+// A block's view of its gang.  gen: barriers passed since the gang was reset.
+struct GangCtx {
+    Gang *gg;
+    int G, gb, groups, grp;
+    unsigned int members;  // blocks of the group
+    unsigned int gen;
+};
+
+__device__ __forceinline__ GangCtx gang_enter(Gang *gg, int G, int gb)
+{
+    GangCtx c;
+    c.gg = gg;
+    c.G = G;
+    c.gb = gb;
+    c.groups = G > BAR_ONE_LEVEL ? BAR_GROUPS : 1;
+    c.grp = gb % c.groups;
+    c.members = (unsigned)((G - c.grp + c.groups - 1) / c.groups);
+    // no block of the gang can pass a barrier before all have read it
+    c.gen = ld_dev(&gg->gen[c.grp].v);
+    return c;
+}
 
 // ---------------------------------------------------------------------------
 // Gang barrier.  Everything a block hands to the others (vector entries,
 // histogram merges, partials, clears) is written with device-scope atomics
 // or write-through stores and read with device-scope loads, so arriving
 // needs only the block's own memory operations to have completed
-// (vmem_drain) and leaving needs no cache invalidation.  A gang of more than
-// BAR_TWO_LEVEL blocks arrives in two levels: each block on the counter of
-// its group (gb mod BAR_GROUPS), the last of a group on the gang counter, so
-// no counter takes more than G / BAR_GROUPS serialised atomics.
+// (vmem_drain) and leaving needs no cache invalidation.  The barrier numbered
+// gen is complete when each group's counter has reached (gen + 1) * members
+// and the groups' counter (gen + 1) * groups.
 //
-// gang_barrier_then: the last block to arrive runs work() with all its
-// threads before it releases the others.  Reductions over the whole gang
-// (the blocks' records, histogram copies, partials) are done there once,
-// and every other block reads only the result: when every block reads all
-// G contributions the same words are fetched G times at once.
-template <class Work>
-__device__ bool gang_barrier_then(Gang *gg, int G, int gb, Work &&work)
+// group_work() is run by the last block of a large gang's group before the
+// group counts as arrived.  Returns true in every thread of the last block to
+// arrive; what that block has done by then, and does before it releases the
+// others, happens once for the gang.
+template <bool GW, class GroupWork>
+__device__ __forceinline__ bool gang_arrive(const GangCtx &c, GroupWork &&group_work)
 {
-    __shared__ int s_ok, s_last;
-    __shared__ unsigned int s_gen;
+    __shared__ int s_last;
     vmem_drain();
     __syncthreads();
+    Gang *gg = c.gg;
+    auto count = [](unsigned int *w) {
+        return __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    };
     if (threadIdx.x == 0) {
-        const unsigned int gen = ld_dev(&gg->bar_gen);
-        bool last;
-        if (G > BAR_TWO_LEVEL) {
-            const int grp = gb % BAR_GROUPS;
-            const unsigned int members = (unsigned)((G - grp + BAR_GROUPS - 1) / BAR_GROUPS);
-            unsigned int *sc = &gg->bar_sub[grp][0];
-            last = false;
-            if (__hip_atomic_fetch_add(sc, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
-                members) {
-                // re-arm the group counter before the gang can be released
-                // (its members wait for the generation below)
-                st_dev(sc, 0u);
-                vmem_drain();
-                last = __hip_atomic_fetch_add(&gg->bar_count, 1u, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT) + 1 ==
-                       (unsigned)BAR_GROUPS;
-            }
-        } else {
-            last = __hip_atomic_fetch_add(&gg->bar_count, 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)G;
-        }
-        s_ok = 1;
-        s_last = last ? 1 : 0;
-        s_gen = gen;
+        bool last = count(&gg->sub[c.grp].v) == (c.gen + 1u) * c.members;
+        if (!GW && last && c.groups > 1)
+            last = count(&gg->top.v) == (c.gen + 1u) * (unsigned)c.groups;
+        s_last = last;
     }
     __syncthreads();
-    if (s_last) {
+    bool last = s_last != 0;
+    if (GW && last && c.groups > 1) {
+        group_work();
+        vmem_drain();
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = count(&gg->top.v) == (c.gen + 1u) * (unsigned)c.groups;
+        __syncthreads();
+        last = s_last != 0;
+    }
+    return last;
+}
+
+// Polls until ready() or the spin limit; false when the gang has given up.
+template <class Ready>
+__device__ __forceinline__ bool gang_poll(Gang *gg, Ready &&ready)
+{
+    unsigned int spins = 0;
+    while (!ready()) {
+        if ((++spins & 63u) == 0u && (ld_dev(&gg->abort) || spins > SPIN_LIMIT)) {
+            __hip_atomic_fetch_or(&gg->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return true;
+}
+
+// The barrier; the last block to arrive runs work() with all its threads
+// before it releases the others.
+template <bool GW, class GroupWork, class Work>
+__device__ __forceinline__ bool gang_barrier_with(GangCtx &c, GroupWork &&group_work, Work &&work)
+{
+    __shared__ int s_ok;
+    Gang *gg = c.gg;
+    const unsigned int next = c.gen + 1u;
+    if (gang_arrive<GW>(c, group_work)) {
         work();
         vmem_drain();
         __syncthreads();
-        if (threadIdx.x == 0) {
-            st_dev(&gg->bar_count, 0u);
-            vmem_drain();
-            st_dev(&gg->bar_gen, s_gen + 1);
-        }
-    } else if (threadIdx.x == 0) {
-        unsigned int spins = 0;
-        while (ld_dev(&gg->bar_gen) == s_gen) {
-            if (ld_dev(&gg->abort) || ++spins > SPIN_LIMIT) {
-                __hip_atomic_fetch_or(&gg->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_ok = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
+        if ((int)threadIdx.x < c.groups) st_dev(&gg->gen[threadIdx.x].v, next);
+        c.gen = next;
+        return true;
     }
+    if (threadIdx.x == 0) s_ok = gang_poll(gg, [&] { return ld_dev(&gg->gen[c.grp].v) == next; });
     __syncthreads();
+    c.gen = next;
     return s_ok != 0;
 }
 
-__device__ __forceinline__ bool gang_barrier(Gang *gg, int G, int gb)
+template <class Work>
+__device__ __forceinline__ bool gang_barrier_then(GangCtx &c, Work &&work)
 {
-    return gang_barrier_then(gg, G, gb, [] {});
+    return gang_barrier_with<false>(c, [] {}, work);
+}
+
+__device__ __forceinline__ bool gang_barrier(GangCtx &c)
+{
+    return gang_barrier_then(c, [] {});
+}
+
+// A barrier that hands out one value: work() returns it in thread 0 of the
+// last block to arrive, and the others poll for it (buffer k).  The value of
+// the other buffer, which every block has read by then, is taken back.
+template <class Work>
+__device__ __forceinline__ bool gang_publish(GangCtx &c, int k, double &value, Work &&work)
+{
+    __shared__ int s_ok;
+    __shared__ double s_v;
+    Gang *gg = c.gg;
+    const bool last = gang_arrive<false>(c, [] {});
+    if (last) {
+        const double v = work();
+        if (threadIdx.x == 0) s_v = v;
+        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k ^ 1][threadIdx.x].w, NO_VALUE);
+        vmem_drain();
+        __syncthreads();
+        unsigned long long bits = (unsigned long long)__double_as_longlong(s_v);
+        if (bits == NO_VALUE) bits = 0x7ff8000000000000ull;
+        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k][threadIdx.x].w, bits);
+        if (threadIdx.x == 0) s_ok = 1;
+    } else if (threadIdx.x == 0) {
+        unsigned long long bits = NO_VALUE;
+        s_ok = gang_poll(gg, [&] {
+            bits = ld_dev(&gg->val[k][c.grp].w);
+            return bits != NO_VALUE;
+        });
+        s_v = __longlong_as_double((long long)bits);
+    }
+    __syncthreads();
+    c.gen++;
+    value = s_v;
+    const bool ok = s_ok != 0;
+    __syncthreads();
+    return ok;
 }
 
 struct DotOut {
@@ -169,207 +248,240 @@ struct DotOut {
 };
 
 // Shared-memory workspace of one block (CG and batched kernels).
-struct CgLds {
-    // the key slots, the spare slot W, and three more words (the batched
-    // kernel counts signs and non-finite products there, qdot_select.hpp)
+template <int NT>
+struct CgLdsT {
+    // the key slots and the counts behind them (qdot_select.hpp); zero
+    // between the uses
     alignas(16) unsigned int h[4 * FQ];
     unsigned char lut[W_LUT];
-    Acc red[3][BLOCK / 64];
-    int4 scratch[BLOCK / 64];
+    Acc red[3][NT / 64];
+    int4 scratch[NT / 64];
+    SelLds<NT> sel;
     qdot_result res;
-    double dval;
-    double sval;  // S of the last qdot combine (units of 2^e_max)
 };
 
-// Pass 1 of qdot for one component pair, into the block's LDS histogram.
-__device__ __forceinline__ void scan_pair(double a, double b, int key_mode, CgLds &L,
-                                          unsigned int &nz, unsigned int &bad, unsigned int &sg)
+// Pass 1 of qdot for one component pair, into the block's LDS histogram h.
+__device__ __forceinline__ void scan_pair(double a, double b, int key_mode, unsigned int *h,
+                                          unsigned int &sg)
 {
     const Comp c = component(a, b, key_mode);
-    nz += c.zero ? 1u : 0u;
-    bad |= c.bad ? 1u : 0u;
     sg |= c.zero ? 0u : (c.sgn ? 1u : 2u);
-    atomicAdd(&L.h[c.slot], 1u);
+    atomicAdd(&h[c.slot + (c.bad ? 1 : 0)], 1u);
+}
+
+// Groups of 4 NT components in flight per thread in a gang's sweeps: a large
+// block's slice is one group.
+template <int NT>
+constexpr int gang_u()
+{
+    return NT >= 1024 ? 1 : 2;
+}
+
+__device__ __forceinline__ uint4 ld_dev_quad(const uint4 *p)
+{
+    const unsigned long long *w = reinterpret_cast<const unsigned long long *>(p);
+    const unsigned long long a = ld_dev(w), b = ld_dev(w + 1);
+    return make_uint4((unsigned int)a, (unsigned int)(a >> 32), (unsigned int)b,
+                      (unsigned int)(b >> 32));
+}
+
+// The waves' sums of the three classes (red, per wave) merged in the first
+// wave: lane 16 q holds class q's.  A barrier precedes it.
+template <int NT>
+__device__ __forceinline__ Acc merge_waves(Acc (*red)[NT / 64])
+{
+    constexpr int NW = NT / 64;
+    const int lane = threadIdx.x & 63, q = lane >> 4, w = lane & 15;
+    Acc a = {0.0, 0.0};
+    if (q < 3 && w < NW) a = red[q][w];
+    if (NW > 8) a = acc_dpp<DPP_FROM8>(a);
+    if (NW > 4) a = acc_dpp<DPP_FROM4>(a);
+    a = acc_dpp<DPP_FROM2>(a);
+    return acc_dpp<DPP_FROM1>(a);
 }
 
 // a.b over the gang's rows by qdot (buffer k), value identical in every block.
 // With `scanned` the caller has already put its rows' keys into L.h (while
-// it produced a or b) and passes its zero count, non-finite flag and sign
-// bits.  After the histogram merge each block copies the merged window into
-// its LDS histogram (counts of one system fit 32 bits) and selects from
-// there; the copy is cleared before returning.
+// it produced a or b) and passes its sign bits.  L.h is zero again afterwards.
 //
 // GUARD (guard_mode 1): after the combine every block evaluates the lower
-// bound of Thm 3.4 from its copy of the histogram and its class table, and
+// bound of Thm 3.4 from its copy of the counts and its class table, and
 // certifies the result or reselects against E_lo (or makes every bin
 // double) and sums its rows again, into the other partials buffer (free:
 // every block has read it in the previous inner product), then checks again
 // with the larger lower bound: the steps and flags of the single-vector
 // guaranteed mode, one more gang barrier when it reselects.
-template <bool GUARD>
+template <bool GUARD, int NT>
 __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, int64_t n,
-                                            int64_t r0, int64_t r1, double tol, int key_mode,
-                                            int score_mode, int nonstrict, Gang *gg,
-                                            int G, int gb, int k, CgLds &L,
+                                            int64_t r0, int64_t r1, const SelArgs &sa,
+                                            GangCtx &c, int k, CgLdsT<NT> &L,
                                             qdot_result *trace_slot, bool scanned = false,
-                                            unsigned int nz = 0, unsigned int bad = 0,
                                             unsigned int sg = 0)
 {
+    constexpr int U = gang_u<NT>();
+    constexpr int K = (FQ + NT - 1) / NT;
     DotOut o = {0.0, false, true};
+    Gang *gg = c.gg;
     GangQ &Q = gg->qb[k];
+    const int tid = threadIdx.x;
+    uint4 *h4 = reinterpret_cast<uint4 *>(L.h);
     const bool vec = ((((uintptr_t)a) | ((uintptr_t)bv)) & 15) == 0;
-    if (!scanned) {
-        // pass 1 over own rows
-        auto scan = [&](const double *xv, const double *yv, int64_t, int lim) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const Comp c = component(xv[e], yv[e], key_mode);
-                const bool valid = e < lim;
-                nz += (valid & c.zero) ? 1u : 0u;
-                bad |= (valid & c.bad) ? 1u : 0u;
-                sg |= (valid & !c.zero) ? (c.sgn ? 1u : 2u) : 0u;
-                if (valid) atomicAdd(&L.h[c.slot], 1u);
-            }
-        };
-        if (vec)
-            stream_strided<true, 2>(a, bv, r0, 2 * CHUNK, r1, scan);
-        else
-            stream_strided<false, 2>(a, bv, r0, 2 * CHUNK, r1, scan);
-    }
+    auto sweep_rows = [&](auto &&body) {
+        if (vec) stream_strided<true, U, NT>(a, bv, r0, (int64_t)U * NT * EPT, r1, body);
+        else stream_strided<false, U, NT>(a, bv, r0, (int64_t)U * NT * EPT, r1, body);
+    };
+    if (!scanned)
+        sweep_rows([&](const double *xv, const double *yv, int64_t, int lim) {
+            count4(xv, yv, lim, sa.key_mode, L.h, sg);
+        });
+    count_signs(sg, L.h);
+    select_begin(L.sel);
     __syncthreads();
-    int lo = W, hi = -1;
-    for (int j = threadIdx.x; j < W; j += BLOCK) {
-        const unsigned int v = L.h[j];
-        if (v) {
-            __hip_atomic_fetch_add(&Q.hist[gb % GANG_HIST_COPIES][j], v, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            L.h[j] = 0u;
-            lo = min(lo, j);
-            hi = max(hi, j);
+    // the block's counts into its group's, or a small gang's own
+    {
+        unsigned int *gh =
+            reinterpret_cast<unsigned int *>(c.groups > 1 ? Q.hist[c.grp] : Q.hm);
+        for (int j = tid; j < 4 * FQ; j += NT) {
+            const unsigned int v = L.h[j];
+            if (v)
+                __hip_atomic_fetch_add(&gh[j], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    if (threadIdx.x == 0) L.h[W] = 0u;
-    // the block's record, a plain write-through store: same-word atomics of
-    // every block would queue at one address, and the wait for them before
-    // the barrier would put that whole queue on every block's path
-    unsigned int bs = (bad ? 1u : 0u) | (sg << 1);
-    block_reduce_range(lo, hi, nz, bs, L.scratch);
-    if (threadIdx.x == 0) {
-        int *rec = &Q.rec[gb].x;
-        st_dev(rec, lo);
-        st_dev(rec + 1, hi);
-        st_dev(rec + 2, (int)nz);
-        st_dev(rec + 3, (int)bs);
-    }
-    // the last block to arrive reduces the gang's records (counts of one
-    // system fit 32 bits), sums the histogram copies over the live window
-    // into hm and clears the copies for the qdot after next
-    auto merge = [&]() {
-        int lo2 = W, hi2 = -1;
-        unsigned int z2 = 0, bs2 = 0;
-        for (int c = threadIdx.x; c < G; c += BLOCK) {
-            const int *rec = &Q.rec[c].x;
-            lo2 = min(lo2, ld_dev(rec));
-            hi2 = max(hi2, ld_dev(rec + 1));
-            z2 += (unsigned int)ld_dev(rec + 2);
-            bs2 |= (unsigned int)ld_dev(rec + 3);
+    // a group's last block adds the group's counts to the gang's and clears
+    // them for the qdot after next
+    auto merge_group = [&]() {
+        unsigned int *gh = reinterpret_cast<unsigned int *>(Q.hist[c.grp]);
+        unsigned int *gm = reinterpret_cast<unsigned int *>(Q.hm);
+        unsigned int m[4 * K];
+#pragma unroll
+        for (int i = 0; i < 4 * K; i++) {
+            const int j = i * NT + tid;
+            m[i] = j < 4 * FQ ? ld_dev(&gh[j]) : 0u;
         }
-        block_reduce_range(lo2, hi2, z2, bs2, L.scratch);
-        const int ncopy = min(G, GANG_HIST_COPIES);
-        for (int j = lo2 + (int)threadIdx.x; j <= hi2; j += BLOCK) {
-            unsigned int v = 0u;
-            for (int c = 0; c < ncopy; c++) {
-                v += ld_dev(&Q.hist[c][j]);
-                st_dev(&Q.hist[c][j], 0u);
+#pragma unroll
+        for (int i = 0; i < 4 * K; i++) {
+            const int j = i * NT + tid;
+            if (m[i]) {
+                __hip_atomic_fetch_add(&gm[j], m[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                st_dev(&gh[j], 0u);
             }
-            st_dev(&Q.hm[j], v);
-        }
-        if (threadIdx.x == 0) {
-            int *sm = &Q.sum.x;
-            st_dev(sm, lo2);
-            st_dev(sm + 1, hi2);
-            st_dev(sm + 2, (int)z2);
-            st_dev(sm + 3, (int)bs2);
         }
     };
-    if (!gang_barrier_then(gg, G, gb, merge)) {
+    if (!gang_barrier_with<true>(c, merge_group, [] {})) {
         o.ok = false;
         return o;
     }
-    // the merged window into this block's LDS copy
-    const int glo = ld_dev(&Q.sum.x);
-    const int ghi = ld_dev(&Q.sum.y);
-    const unsigned long long gnz = (unsigned int)ld_dev(&Q.sum.z);
-    const unsigned int gbs = (unsigned int)ld_dev(&Q.sum.w);
-    const unsigned int gbad = gbs & 1u;
-    const unsigned int gsg = gbs >> 1;
-    for (int j = glo + (int)threadIdx.x; j <= ghi; j += BLOCK) L.h[j] = ld_dev(&Q.hm[j]);
+    // the merged counts into LDS, and the selection, in every block
+    {
+        uint4 v[K];
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const int q = i * NT + tid;
+            v[i] = q < FQ ? ld_dev_quad(&Q.hm[q]) : make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int i = 0; i < K; i++)
+            if (i * NT + tid < FQ) h4[i * NT + tid] = v[i];
+        find_window<NT, K>(v, L.sel);
+    }
     __syncthreads();
-    // cutoff, redundantly in every block, into the block's own class table
-    auto get = [&](int j) { return (unsigned long long)L.h[j]; };
-    auto put = [&](int j, int c) { L.lut[j] = (unsigned char)c; };
-    auto noclear = [&](int) {};
-    const CutParams p = block_cutoff<BLOCK>(glo, ghi, gnz, gbad, n, tol, score_mode, nonstrict,
-                                            get, put, noclear, &L.res, nullptr);
-    // pass 2 over own rows into partials buffer kp, combine in every block
-    auto sweep = [&](const CutParams &cp, int kp, int flags) -> bool {
-        Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-        auto body = [&](const double *xv, const double *yv, int64_t, int lim) {
-            acc_group<false>(xv, yv, lim, L.lut, key_mode, cp.e_max, cp.c32, true, acc[0],
-                             acc[1], acc[2], nullptr);
-        };
-        if (vec)
-            stream_strided<true, 2>(a, bv, r0, 2 * CHUNK, r1, body);
-        else
-            stream_strided<false, 2>(a, bv, r0, 2 * CHUNK, r1, body);
-        block_reduce3<BLOCK>(acc, L.red);
-        if (threadIdx.x == 0) {
-            double *pp = gg->partials[kp] + gb * 6;
-            for (int q = 0; q < 3; q++) {
-                st_dev(&pp[2 * q], acc[q].s);
-                st_dev(&pp[2 * q + 1], acc[q].c);
-            }
-        }
-        // the last block to arrive combines the gang's partials in block
-        // order; every block then finishes from the same six words
-        auto combine = [&]() {
-            Acc f[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-            for (int c = threadIdx.x; c < G; c += BLOCK) {
-                const double *pp = gg->partials[kp] + c * 6;
-                for (int q = 0; q < 3; q++)
-                    f[q] = acc_merge(f[q], Acc{ld_dev(&pp[2 * q]), ld_dev(&pp[2 * q + 1])});
-            }
-            block_reduce3<BLOCK>(f, L.red);
-            if (threadIdx.x == 0)
-                for (int q = 0; q < 3; q++) {
-                    st_dev(&gg->pfin[kp][2 * q], f[q].s);
-                    st_dev(&gg->pfin[kp][2 * q + 1], f[q].c);
-                }
-        };
-        if (!gang_barrier_then(gg, G, gb, combine)) return false;
-        if (threadIdx.x == 0) {
-            Acc f[3];
-            for (int q = 0; q < 3; q++)
-                f[q] = Acc{ld_dev(&gg->pfin[kp][2 * q]), ld_dev(&gg->pfin[kp][2 * q + 1])};
-            L.sval = combine_value(f, cp.e_max, cp.c32, flags, &L.res);
-        }
-        return true;
+    const Sel s = select_classes<NT>(L.h, sa, L.sel, L.lut);
+    const int lo = s.n_bins ? s.e_min - KMIN : W, hi = s.n_bins ? s.e_max - KMIN : -1;
+    // the last block to arrive after the sweep clears the merged counts
+    auto clear_counts = [&]() {
+        unsigned int *gm = reinterpret_cast<unsigned int *>(Q.hm);
+        for (int j = lo + tid; j <= hi; j += NT) st_dev(&gm[j], 0u);
+        if (tid < 4) st_dev(&gm[W + tid], 0u);
     };
-    if (threadIdx.x == 0) L.sval = 0.0;
-    if (!p.skip) {
-        if (!sweep(p, k, p.flags)) {
+    // pass 2 over own rows into partials buffer kp
+    auto sweep = [&](int e_max, int c32, int kp) {
+        Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+        sweep_rows([&](const double *xv, const double *yv, int64_t, int lim) {
+            acc_group<false>(xv, yv, lim, L.lut, sa.key_mode, e_max, c32, true, acc[0], acc[1],
+                             acc[2], nullptr);
+        });
+        block_reduce3_waves<NT, false>(acc, L.red);
+        __syncthreads();
+        if (tid < 64) {
+            const Acc b = merge_waves<NT>(L.red);
+            const int q = tid >> 4;
+            if ((tid & 15) == 0 && q < 3) {
+                double *pp = gg->partials[kp];
+                st_dev(&pp[(2 * q) * c.G + c.gb], b.s);
+                st_dev(&pp[(2 * q + 1) * c.G + c.gb], b.c);
+            }
+        }
+    };
+    // the gang's partials in block order, by the last block to arrive: the
+    // classes' sums into pfin, and the combined value in thread 0
+    auto combine = [&](int e_max, int c32, int kp) -> double {
+        Acc f[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+        const double *pp = gg->partials[kp];
+        for (int b = tid; b < c.G; b += NT)
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+                f[q] = acc_merge(f[q], Acc{ld_dev(&pp[(2 * q) * c.G + b]),
+                                           ld_dev(&pp[(2 * q + 1) * c.G + b])});
+        block_reduce3_waves<NT, true>(f, L.red);
+        __syncthreads();
+        double v = 0.0;
+        if (tid < 64) {
+            const Acc b = merge_waves<NT>(L.red);
+            Acc t[3];
+#pragma unroll
+            for (int q = 0; q < 3; q++) t[q] = lane_acc(b, 16 * q);
+            if (tid == 0) {
+                for (int q = 0; q < 3; q++) {
+                    st_dev(&gg->pfin[kp][2 * q], t[q].s);
+                    st_dev(&gg->pfin[kp][2 * q + 1], t[q].c);
+                }
+                combine_value(t, e_max, c32, 0, &L.sel.sums);
+                v = L.sel.sums.value;
+            }
+        }
+        return v;
+    };
+    // the whole result in this block's L.res, for the guard and the trace
+    auto fill_result = [&]() {
+        select_count<NT>(L.h, s, sa, L.sel);
+        __syncthreads();
+        if (tid == 0) {
+            result_fields<NT>(s, sa, n, L.sel, L.res);
+            L.sel.sum = 0.0;
+            if (s.live() && s.kept) {
+                Acc f[3];
+                for (int q = 0; q < 3; q++)
+                    f[q] = Acc{ld_dev(&gg->pfin[k][2 * q]), ld_dev(&gg->pfin[k][2 * q + 1])};
+                L.sel.sum = combine_value(f, s.e_max, s.c32, L.res.flags, &L.res);
+            }
+        }
+        __syncthreads();
+    };
+    const bool swept = s.live() && s.kept;
+    if (swept) {
+        sweep(s.e_max, s.c32, k);
+        if (!gang_publish(c, k, o.value, [&] {
+                clear_counts();
+                return combine(s.e_max, s.c32, k);
+            })) {
             o.ok = false;
             return o;
         }
-    } else if (!gang_barrier(gg, G, gb)) {
-        o.ok = false;
-        return o;
+    } else {
+        if (!gang_publish(c, k, o.value, [&] {
+                clear_counts();
+                return s.status != QDOT_OK ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
+            })) {
+            o.ok = false;
+            return o;
+        }
     }
-    __syncthreads();
+    bool all_perf = s.live() && !s.kept;
     if constexpr (GUARD) {
         __shared__ int s_go, s_dref, s_passes;
         __shared__ double s_low;
-        if (threadIdx.x == 0) {
+        fill_result();
+        if (tid == 0) {
             s_go = L.res.status == QDOT_OK && L.res.n_bins > 0;
             // every product zero: +0 is exact
             if (L.res.status == QDOT_OK && L.res.n_bins == 0) L.res.flags |= QDOT_F_GUARANTEED;
@@ -379,17 +491,20 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
         __syncthreads();
         if (s_go) {
             const int e_max = L.res.e_max;
-            const GuardSums g0 = guard_sums<BLOCK>(get, L.lut, glo, ghi, e_max);
-            if (threadIdx.x == 0) {
-                const double low = guard_lower(g0, L.sval, n, gsg);
-                if (guard_certified(L.res.bound_rel, low, tol)) {
+            auto get = [&](int j) { return (unsigned long long)L.h[j]; };
+            auto put = [&](int j, int cls) { L.lut[j] = (unsigned char)cls; };
+            auto noclear = [&](int) {};
+            const GuardSums g0 = guard_sums<NT>(get, L.lut, lo, hi, e_max);
+            if (tid == 0) {
+                const double low = guard_lower(g0, L.sel.sum, n, s.signs);
+                if (guard_certified(L.res.bound_rel, low, sa.tol)) {
                     L.res.flags |= QDOT_F_GUARANTEED;
                     L.res.lower = ldexp(low, e_max);
                 } else {
                     // L <= 0: every bin double (scores >= 23, one more
                     // non-strict)
                     const int ref = low > 0.0 ? e_max + ilogb(low)
-                                              : L.res.e_min - L.res.t - 22 - nonstrict;
+                                              : L.res.e_min - L.res.t - 22 - sa.nonstrict;
                     if (ref < e_max) {
                         s_dref = e_max - ref;
                         s_low = low;
@@ -401,36 +516,54 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
             __syncthreads();
             if (s_dref) {
                 // reselection against e_ref = e_max - dref, second sweep
-                const CutParams p2 = block_cutoff<BLOCK>(glo, ghi, gnz, 0u, n, tol, score_mode,
-                                                         nonstrict, get, put, noclear, &L.res,
-                                                         nullptr, s_dref);
-                if (threadIdx.x == 0) {
+                const CutParams p2 = block_cutoff<NT>(lo, hi, s.n_zero, 0u, n, sa.tol,
+                                                      sa.score_mode, sa.nonstrict, get, put,
+                                                      noclear, &L.res, nullptr, s_dref);
+                if (tid == 0) {
                     L.res.flags |= QDOT_F_RESELECTED;
                     L.res.passes = s_passes + (p2.skip ? 0 : 1);
-                    L.sval = 0.0;
+                    L.sel.sum = 0.0;
                 }
-                if (!p2.skip && !sweep(p2, k ^ 1, p2.flags | QDOT_F_RESELECTED)) {
-                    o.ok = false;
-                    return o;
+                if (!p2.skip) {
+                    sweep(p2.e_max, p2.c32, k ^ 1);
+                    if (!gang_barrier_then(c, [&] { (void)combine(p2.e_max, p2.c32, k ^ 1); })) {
+                        o.ok = false;
+                        return o;
+                    }
+                    if (tid == 0) {
+                        Acc f[3];
+                        for (int q = 0; q < 3; q++)
+                            f[q] = Acc{ld_dev(&gg->pfin[k ^ 1][2 * q]),
+                                       ld_dev(&gg->pfin[k ^ 1][2 * q + 1])};
+                        L.sel.sum = combine_value(f, p2.e_max, p2.c32,
+                                                  p2.flags | QDOT_F_RESELECTED, &L.res);
+                    }
                 }
                 __syncthreads();
-                const GuardSums g1 = guard_sums<BLOCK>(get, L.lut, glo, ghi, e_max);
-                if (threadIdx.x == 0) {
-                    const double low = fmax(guard_lower(g1, L.sval, n, gsg), s_low);
+                const GuardSums g1 = guard_sums<NT>(get, L.lut, lo, hi, e_max);
+                if (tid == 0) {
+                    const double low = fmax(guard_lower(g1, L.sel.sum, n, s.signs), s_low);
                     L.res.flags |= QDOT_F_RESELECTED |
-                                   (guard_certified(L.res.bound_rel, low, tol) ? QDOT_F_GUARANTEED
-                                                                               : 0);
+                                   (guard_certified(L.res.bound_rel, low, sa.tol)
+                                        ? QDOT_F_GUARANTEED
+                                        : 0);
                     L.res.lower = low > 0.0 ? ldexp(low, e_max) : 0.0;
                 }
             }
         }
         __syncthreads();
+        o.value = L.res.value;
+        all_perf = (L.res.flags & QDOT_F_ALL_PERF) && L.res.n_bins > 0;
+    } else if (trace_slot) {
+        fill_result();
     }
-    o.value = L.res.value;
-    o.all_perf = (L.res.flags & QDOT_F_ALL_PERF) && L.res.n_bins > 0;
-    if (threadIdx.x == 0 && trace_slot) *trace_slot = L.res;
-    // the LDS copy of the histogram back to zero for the next scan
-    for (int j = glo + (int)threadIdx.x; j <= ghi; j += BLOCK) L.h[j] = 0u;
+    o.all_perf = all_perf;
+    if (tid == 0 && trace_slot) *trace_slot = L.res;
+    // the LDS counts back to zero for the next scan (all of them: with zero
+    // or non-finite products alone there is no live window)
+    __syncthreads();
+    for (int j = lo + tid; j <= hi; j += NT) L.h[j] = 0u;
+    if (tid < 4) L.h[W + tid] = 0u;
     __syncthreads();
     return o;
 }
@@ -448,12 +581,14 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
 // outside that block, so an inner product costs one gang barrier.
 __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv, int64_t n,
                                                int64_t r0, int64_t r1, double tol, int key_mode,
-                                               int score_mode, int nonstrict, Gang *gg, int G,
-                                               int gb, int k, CgLds &L, S1Lds &S1, double *tab,
+                                               int score_mode, int nonstrict, GangCtx &c, int k,
+                                               CgLdsT<BLOCK> &L, S1Lds &S1, double *tab,
                                                qdot_result *trace_slot)
 {
     DotOut o = {0.0, false, true};
-    GangQ &Q = gg->qb[k];
+    Gang *gg = c.gg;
+    const int G = c.G, gb = c.gb;
+    unsigned int *gh = reinterpret_cast<unsigned int *>(gg->qb[k].hist[gb % BAR_GROUPS]);
     const bool vec = ((((uintptr_t)a) | ((uintptr_t)bv)) & 15) == 0;
     // admitted by the host: depth <= S1_WIN
     const int depth = s1_depth_dev(n, tol, score_mode);
@@ -475,7 +610,7 @@ __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv
     for (int j = threadIdx.x; j < W; j += BLOCK) {
         const unsigned int v = L.h[j];
         if (v) {
-            __hip_atomic_fetch_add(&Q.hist[gb % GANG_HIST_COPIES][j], v, __ATOMIC_RELAXED,
+            __hip_atomic_fetch_add(&gh[j], v, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             L.h[j] = 0u;
             lo = min(lo, j);
@@ -495,29 +630,32 @@ __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv
     unsigned int bs = bad ? 1u : 0u;
     block_reduce_range(lo, hi, nz, bs, L.scratch);
     if (threadIdx.x == 0) {
-        int *rec = &Q.rec[gb].x;
+        int *rec = &gg->rec[k][gb].x;
         st_dev(rec, lo);
         st_dev(rec + 1, hi);
         st_dev(rec + 2, (int)nz);
         st_dev(rec + 3, (int)bs);
     }
     auto finish = [&]() {
+        // the other buffer's value, as gang_publish does
+        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k ^ 1][threadIdx.x].w, NO_VALUE);
         int lo2 = W, hi2 = -1;
         unsigned int z2 = 0, bs2 = 0;
-        for (int c = threadIdx.x; c < G; c += BLOCK) {
-            const int *rec = &Q.rec[c].x;
+        for (int b = threadIdx.x; b < G; b += BLOCK) {
+            const int *rec = &gg->rec[k][b].x;
             lo2 = min(lo2, ld_dev(rec));
             hi2 = max(hi2, ld_dev(rec + 1));
             z2 += (unsigned int)ld_dev(rec + 2);
             bs2 |= (unsigned int)ld_dev(rec + 3);
         }
         block_reduce_range(lo2, hi2, z2, bs2, L.scratch);
-        const int ncopy = min(G, GANG_HIST_COPIES);
+        const int ncopy = min(G, BAR_GROUPS);
         for (int j = lo2 + (int)threadIdx.x; j <= hi2; j += BLOCK) {
             unsigned int v = 0u;
-            for (int c = 0; c < ncopy; c++) {
-                v += ld_dev(&Q.hist[c][j]);
-                st_dev(&Q.hist[c][j], 0u);
+            for (int q = 0; q < ncopy; q++) {
+                unsigned int *hq = reinterpret_cast<unsigned int *>(gg->qb[k].hist[q]);
+                v += ld_dev(&hq[j]);
+                st_dev(&hq[j], 0u);
             }
             L.h[j] = v;
         }
@@ -544,7 +682,7 @@ __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv
             st_dev(reinterpret_cast<unsigned long long *>(&gg->res[k]) + threadIdx.x,
                    reinterpret_cast<const unsigned long long *>(&L.res)[threadIdx.x]);
     };
-    if (!gang_barrier_then(gg, G, gb, finish)) {
+    if (!gang_barrier_then(c, finish)) {
         o.ok = false;
         return o;
     }
@@ -560,107 +698,203 @@ __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv
     return o;
 }
 
-// a.b over the gang's rows in plain FP64 (partials buffer k).
-__device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, int64_t r0, int64_t r1, Gang *gg,
-                             int G, int gb, int k, CgLds &L)
+// a.b over the gang's rows in plain FP64 (buffer k): the blocks' sums added in
+// a fixed order by the last block to arrive.
+template <int NT>
+__device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, int64_t r0,
+                                             int64_t r1, GangCtx &c, int k, CgLdsT<NT> &L)
 {
     DotOut o = {0.0, false, true};
+    Gang *gg = c.gg;
+    const int tid = threadIdx.x;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    int64_t i = r0 + threadIdx.x;
-    for (; i + 3 * BLOCK < r1; i += 4 * BLOCK) {
+    int64_t i = r0 + tid;
+    for (; i + 3 * NT < r1; i += 4 * NT) {
 #pragma unroll
-        for (int u = 0; u < 4; u++) s[u] = fma(a[i + u * BLOCK], bv[i + u * BLOCK], s[u]);
+        for (int u = 0; u < 4; u++) s[u] = fma(a[i + u * NT], bv[i + u * NT], s[u]);
     }
-    for (; i < r1; i += BLOCK) s[0] = fma(a[i], bv[i], s[0]);
-    Acc acc[3] = {{(s[0] + s[1]) + (s[2] + s[3]), 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    block_reduce3<BLOCK>(acc, L.red);
-    if (threadIdx.x == 0) st_dev(&gg->partials[k][gb * 6], acc[0].s + acc[0].c);
-    if (!gang_barrier(gg, G, gb)) {
-        o.ok = false;
-        return o;
-    }
-    // every block sums the gang's partials in the same fixed order (thread
-    // c loads partial c, then a fixed tree), so all hold the same value
-    double v = 0.0;
-    for (int c = threadIdx.x; c < G; c += BLOCK) v += ld_dev(&gg->partials[k][c * 6]);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    if ((threadIdx.x & 63) == 0) L.red[0][threadIdx.x >> 6].s = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double f = L.red[0][0].s;
-        for (int w = 1; w < BLOCK / 64; w++) f += L.red[0][w].s;
-        L.dval = f;
-    }
-    __syncthreads();
-    o.value = L.dval;
-    __syncthreads();
+    for (; i < r1; i += NT) s[0] = fma(a[i], bv[i], s[0]);
+    auto block_sum = [&](double v) {
+        v = wave_sum_d(v);
+        if ((tid & 63) == 0) L.red[0][tid >> 6].s = v;
+        __syncthreads();
+        double f = 0.0;
+        if (tid == 0) {
+            f = L.red[0][0].s;
+            for (int w = 1; w < NT / 64; w++) f += L.red[0][w].s;
+        }
+        __syncthreads();
+        return f;
+    };
+    const double part = block_sum((s[0] + s[1]) + (s[2] + s[3]));
+    if (tid == 0) st_dev(&gg->partials[k][c.gb], part);
+    o.ok = gang_publish(c, k, o.value, [&] {
+        double v = 0.0;
+        for (int b = tid; b < c.G; b += NT) v += ld_dev(&gg->partials[k][b]);
+        return block_sum(v);
+    });
     return o;
 }
 
-// out[i] = sum_j val[j] * v[col[j]] over rows [r0, r1), each row summed in
-// column-storage order (plain multiply, then add).  v may hold entries that
-// other blocks wrote in this launch, so it is read with device-scope loads.
-// A thread takes SR rows at once and issues the column and value loads of
-// their first SNZ entries, then every gather, before it adds: two memory
-// latencies per SR rows instead of two per entry.  Longer rows finish in a
-// plain loop.
-constexpr int SR = 2;
+// ---------------------------------------------------------------------------
+// out[i] = sum_j val[j] * v[col[j]] over the block's rows [r0, r1), each row
+// summed in column-storage order (plain multiply, then add).  v may hold
+// entries that other blocks wrote in this launch, so it is read with
+// device-scope loads.
+//
+// A thread issues the gathers of its row's first SNZ entries before it adds.
+// The matrix stays the same through the solve, so as many of the block's
+// entries as fit are kept in LDS (the resident rows, the first n_res of the
+// slice), and the first row per thread after them is loaded into registers
+// before the barrier that completes v: of the three round trips of a row
+// (bounds, entries, gathers) only the gathers are left behind the barrier.
+// Rows after those, and the entries past SNZ of long rows, take the three.
+//
+// Poisson 1024^2 (256 blocks of 1024 threads, 4096 rows each, half of them
+// resident), per iteration with the two-pass qdot: 53.7 us; 64 with every
+// entry read behind the barrier (the SpMV 20.5 of them), 66 with the products
+// of coalesced entries staged through LDS.  Two rows per thread in flight
+// spilled: 69.8.
+// ---------------------------------------------------------------------------
+constexpr int SR = 1;
 constexpr int SNZ = 8;
-// With SCAN the row result is also keyed against v's own entry (pass 1 of
-// the qdot v . out that follows, fused here so that v and out are not read
-// again for it).
-template <bool SCAN = false>
-__device__ __forceinline__ void spmv_rows(const CgSys &S, const double *v, double *out, int64_t r0,
-                                          int64_t r1, int key_mode = 0, CgLds *L = nullptr,
-                                          unsigned int *nz = nullptr, unsigned int *bad = nullptr,
-                                          unsigned int *sg = nullptr)
+
+struct Rows {  // SR rows of one thread
+    int beg[SR], len[SR];
+    int ci[SR][SNZ];
+    double pv[SR][SNZ];
+};
+
+// Bounds and first entries of rows base + u NT + tid below r1.
+template <int NT>
+__device__ __forceinline__ void load_rows(const CgSys &S, int64_t base, int64_t r1, Rows &R)
 {
-    for (int64_t base = r0; base < r1; base += (int64_t)SR * BLOCK) {
-        int32_t beg[SR], len[SR];
 #pragma unroll
-        for (int u = 0; u < SR; u++) {
-            const int64_t i = base + u * BLOCK + threadIdx.x;
-            beg[u] = 0;
-            len[u] = 0;
-            if (i < r1) {
-                beg[u] = S.rowptr[i];
-                len[u] = S.rowptr[i + 1] - beg[u];
+    for (int u = 0; u < SR; u++) {
+        const int64_t i = base + u * NT + threadIdx.x;
+        R.beg[u] = 0;
+        R.len[u] = 0;
+        if (i < r1) {
+            R.beg[u] = S.rowptr[i];
+            R.len[u] = S.rowptr[i + 1] - R.beg[u];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < SR; u++)
+#pragma unroll
+        for (int jj = 0; jj < SNZ; jj++) {
+            R.ci[u][jj] = 0;
+            R.pv[u][jj] = 0.0;
+            if (jj < R.len[u]) {
+                R.ci[u][jj] = S.col[R.beg[u] + jj];
+                R.pv[u][jj] = S.val[R.beg[u] + jj];
             }
         }
-        int32_t ci[SR][SNZ];
-        double pv[SR][SNZ];
+}
+
+// The block's resident rows in LDS.
+template <int NT, int LE>
+struct MatLds {
+    static constexpr int ROWS = LE / 2;  // resident rows at most
+    double val[LE > 0 ? LE : 1];
+    int col[LE > 0 ? LE : 1];
+    unsigned short off[ROWS + 1];        // entries before row r0 + i
+    int n_res;
+};
+
+template <int NT, int LE>
+__device__ __forceinline__ void mat_load(const CgSys &S, int64_t r0, int64_t r1,
+                                         MatLds<NT, LE> &M)
+{
+    static_assert(LE < 65536, "16-bit offsets");
+    const int tid = threadIdx.x;
+    if (tid == 0) M.n_res = 0;
+    __syncthreads();
+    if (r0 >= r1) return;
+    const int e0 = S.rowptr[r0];
+    const int ne = min(S.rowptr[r1] - e0, LE);
+    for (int j = tid; j < ne; j += NT) {
+        M.col[j] = S.col[e0 + j];
+        M.val[j] = S.val[e0 + j];
+    }
+    const int nr = (int)min(r1 - r0, (int64_t)M.ROWS);
+    int last = 0;
+    for (int i = tid; i <= nr; i += NT) {
+        const int o = S.rowptr[r0 + i] - e0;
+        if (o <= LE) {
+            M.off[i] = (unsigned short)o;
+            last = i;  // rows below i are resident
+        }
+    }
+    last = wave_reduce_i(last, [](int p, int q) { return max(p, q); });
+    if ((tid & 63) == 0) atomicMax(&M.n_res, last);
+    __syncthreads();
+}
+
+// R: load_rows of the rows after the resident ones, taken before the barrier
+// that completed v.  own(i, yi) is called once per row with its result.
+template <int NT, int LE, class Own>
+__device__ __forceinline__ void spmv_rows(const CgSys &S, const double *v, int64_t r0, int64_t r1,
+                                          const MatLds<NT, LE> &M, Rows &R, Own &&own)
+{
+    const int tid = threadIdx.x;
+    const int n_res = M.n_res;
+    for (int base = 0; base < n_res; base += SR * NT) {
+        double g[SR][SNZ];
+        int beg[SR], len[SR];
+#pragma unroll
+        for (int u = 0; u < SR; u++) {
+            const int i = base + u * NT + tid;
+            beg[u] = 0;
+            len[u] = 0;
+            if (i < n_res) {
+                beg[u] = M.off[i];
+                len[u] = M.off[i + 1] - beg[u];
+            }
+        }
 #pragma unroll
         for (int u = 0; u < SR; u++)
 #pragma unroll
             for (int jj = 0; jj < SNZ; jj++) {
-                ci[u][jj] = 0;
-                pv[u][jj] = 0.0;
-                if (jj < len[u]) {
-                    ci[u][jj] = S.col[beg[u] + jj];
-                    pv[u][jj] = S.val[beg[u] + jj];
-                }
+                g[u][jj] = 0.0;
+                if (jj < len[u]) g[u][jj] = ld_dev(&v[M.col[beg[u] + jj]]);
             }
-#pragma unroll
-        for (int u = 0; u < SR; u++)
-#pragma unroll
-            for (int jj = 0; jj < SNZ; jj++)
-                if (jj < len[u]) pv[u][jj] = pv[u][jj] * ld_dev(&v[ci[u][jj]]);
 #pragma unroll
         for (int u = 0; u < SR; u++) {
             double s = 0.0;
 #pragma unroll
             for (int jj = 0; jj < SNZ; jj++)
-                if (jj < len[u]) s = s + pv[u][jj];
-            for (int32_t j = beg[u] + SNZ; j < beg[u] + len[u]; j++) {
+                if (jj < len[u]) {
+                    const double pr = M.val[beg[u] + jj] * g[u][jj];
+                    s = s + pr;
+                }
+            for (int j = beg[u] + SNZ; j < beg[u] + len[u]; j++) {
+                const double pr = M.val[j] * ld_dev(&v[M.col[j]]);
+                s = s + pr;
+            }
+            const int i = base + u * NT + tid;
+            if (i < n_res) own(r0 + i, s);
+        }
+    }
+    for (int64_t base = r0 + n_res; base < r1; base += SR * NT) {
+        if (base != r0 + n_res) load_rows<NT>(S, base, r1, R);
+#pragma unroll
+        for (int u = 0; u < SR; u++)
+#pragma unroll
+            for (int jj = 0; jj < SNZ; jj++)
+                if (jj < R.len[u]) R.pv[u][jj] = R.pv[u][jj] * ld_dev(&v[R.ci[u][jj]]);
+#pragma unroll
+        for (int u = 0; u < SR; u++) {
+            double s = 0.0;
+#pragma unroll
+            for (int jj = 0; jj < SNZ; jj++)
+                if (jj < R.len[u]) s = s + R.pv[u][jj];
+            for (int j = R.beg[u] + SNZ; j < R.beg[u] + R.len[u]; j++) {
                 const double pr = S.val[j] * ld_dev(&v[S.col[j]]);
                 s = s + pr;
             }
-            const int64_t i = base + u * BLOCK + threadIdx.x;
-            if (i < r1) {
-                out[i] = s;
-                if (SCAN) scan_pair(v[i], s, key_mode, *L, *nz, *bad, *sg);
-            }
+            const int64_t i = base + u * NT + tid;
+            if (i < r1) own(i, s);
         }
     }
 }
@@ -669,9 +903,10 @@ __device__ __forceinline__ void spmv_rows(const CgSys &S, const double *v, doubl
 // ACC1: every inner product by the one-pass qdot (gang_qdot_s1, with the
 // caller's LDS window S1 and the gang's table tab, 2 W S1_PIECES doubles);
 // otherwise by the two-pass qdot, guaranteed with GUARD.
-template <bool GUARD, bool ACC1 = false>
+template <bool GUARD, int NT, int LE, bool ACC1 = false>
 __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb, int key_mode,
-                                         int score_mode, int nonstrict, CgLds &L,
+                                         int score_mode, int nonstrict, CgLdsT<NT> &L,
+                                         MatLds<NT, LE> &M,
                                          qdot_cg_result *res, S1Lds *S1 = nullptr,
                                          double *tab = nullptr)
 {
@@ -681,20 +916,20 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     const int64_t r0 = min(n, (int64_t)gb * per), r1 = min(n, r0 + per);
     int k = 0;  // qdot buffer / partials parity
     int ntr = 0;
-    auto dot = [&](const double *a, const double *bv, bool scanned = false, unsigned int nz = 0,
-                   unsigned int bad = 0, unsigned int sg = 0) {
+    GangCtx c = gang_enter(gg, G, gb);
+    const SelArgs sa = {key_mode, score_mode, nonstrict, 0, S.qtol};
+    auto dot = [&](const double *a, const double *bv, bool scanned = false, unsigned int sg = 0) {
         DotOut o;
         if (S.use_qdot) {
             qdot_result *ts = (gb == 0 && S.trace) ? S.trace + ntr : nullptr;
             if constexpr (ACC1)
-                o = gang_qdot_s1(a, bv, n, r0, r1, S.qtol, key_mode, score_mode, nonstrict, gg,
-                                 G, gb, k, L, *S1, tab + (size_t)k * W * S1_PIECES, ts);
+                o = gang_qdot_s1(a, bv, n, r0, r1, S.qtol, key_mode, score_mode, nonstrict, c, k,
+                                 L, *S1, tab + (size_t)k * W * S1_PIECES, ts);
             else
-                o = gang_qdot<GUARD>(a, bv, n, r0, r1, S.qtol, key_mode, score_mode, nonstrict,
-                                     gg, G, gb, k, L, ts, scanned, nz, bad, sg);
+                o = gang_qdot<GUARD, NT>(a, bv, n, r0, r1, sa, c, k, L, ts, scanned, sg);
             ntr++;
         } else {
-            o = gang_dot64(a, bv, r0, r1, gg, G, gb, k, L);
+            o = gang_dot64<NT>(a, bv, r0, r1, c, k, L);
         }
         k ^= 1;
         return o;
@@ -702,25 +937,27 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     int status = QDOT_OK, iters = 0;
     bool healthy = true;
     // r0 = b - A x0, p0 = r0
-    spmv_rows(S, S.x, S.q, r0, r1);
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += BLOCK) {
-        const double v = S.b[i] - S.q[i];
+    mat_load<NT, LE>(S, r0, r1, M);
+    Rows R;
+    load_rows<NT>(S, r0 + M.n_res, r1, R);
+    spmv_rows<NT, LE>(S, S.x, r0, r1, M, R, [&](int64_t i, double yi) {
+        const double v = S.b[i] - yi;
         S.r[i] = v;
         st_dev(&S.p[i], v);
-    }
+    });
     __syncthreads();
-    DotOut bb = gang_dot64(S.b, S.b, r0, r1, gg, G, gb, k, L);
+    DotOut bb = gang_dot64<NT>(S.b, S.b, r0, r1, c, k, L);
     k ^= 1;
     const double bnorm = sqrt(bb.value);
     const double thresh = S.rtol * bnorm;
     DotOut c0 = dot(S.r, S.r);
     healthy = bb.ok && c0.ok;
-    double c = c0.value;
+    double rr = c0.value;
     bool done = false;
     if (healthy && c0.all_perf) {
         status = QDOT_E_BREAKDOWN;
         done = true;
-    } else if (healthy && !(sqrt(c) > thresh)) {
+    } else if (healthy && !(sqrt(rr) > thresh)) {
         done = true;
     }
     while (healthy && !done) {
@@ -728,26 +965,27 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
             status = QDOT_E_MAXIT;
             break;
         }
-        if (!(healthy = gang_barrier(gg, G, gb))) break;  // p complete
+        load_rows<NT>(S, r0 + M.n_res, r1, R);
+        if (!(healthy = gang_barrier(c))) break;  // p complete
         // pass 1 of the two-pass qdot(p, q) rides in the SpMV; the one-pass
         // qdot reads its rows itself
         const bool scan_q = S.use_qdot != 0 && !ACC1;
-        unsigned int nz1 = 0, bad1 = 0, sg1 = 0;
-        if (scan_q)
-            spmv_rows<true>(S, S.p, S.q, r0, r1, key_mode, &L, &nz1, &bad1, &sg1);
-        else
-            spmv_rows(S, S.p, S.q, r0, r1);
+        unsigned int sg1 = 0;
+        spmv_rows<NT, LE>(S, S.p, r0, r1, M, R, [&](int64_t i, double yi) {
+            S.q[i] = yi;
+            if (scan_q) scan_pair(S.p[i], yi, key_mode, L.h, sg1);
+        });
         __syncthreads();
-        const DotOut d = dot(S.p, S.q, scan_q, nz1, bad1, sg1);
+        const DotOut d = dot(S.p, S.q, scan_q, sg1);
         if (!(healthy = d.ok)) break;
         if (!(d.value > 0.0) || !isfinite(d.value) || d.all_perf) {
             status = QDOT_E_BREAKDOWN;
             break;
         }
-        const double alpha = c / d.value;
+        const double alpha = rr / d.value;
         // x += alpha p, r -= alpha q (four rows' loads in flight per thread),
         // with pass 1 of the qdot r . r that follows fused in
-        unsigned int nz2 = 0, bad2 = 0, sg2 = 0;
+        unsigned int sg2 = 0;
         const bool scan_r = S.use_qdot != 0 && !ACC1;
         auto xr_row = [&](int64_t i, double pi, double xi, double qi, double ri) {
             const double ap = alpha * pi;
@@ -755,64 +993,65 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
             const double aq = alpha * qi;
             const double rn = ri - aq;
             S.r[i] = rn;
-            if (scan_r) scan_pair(rn, rn, key_mode, L, nz2, bad2, sg2);
+            if (scan_r) scan_pair(rn, rn, key_mode, L.h, sg2);
         };
         {
             int64_t i = r0 + threadIdx.x;
-            for (; i + 3 * BLOCK < r1; i += 4 * BLOCK) {
+            for (; i + 3 * NT < r1; i += 4 * NT) {
                 double pi[4], xi[4], qi[4], ri[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    pi[u] = S.p[i + u * BLOCK];
-                    xi[u] = S.x[i + u * BLOCK];
-                    qi[u] = S.q[i + u * BLOCK];
-                    ri[u] = S.r[i + u * BLOCK];
+                    pi[u] = S.p[i + u * NT];
+                    xi[u] = S.x[i + u * NT];
+                    qi[u] = S.q[i + u * NT];
+                    ri[u] = S.r[i + u * NT];
                 }
 #pragma unroll
-                for (int u = 0; u < 4; u++) xr_row(i + u * BLOCK, pi[u], xi[u], qi[u], ri[u]);
+                for (int u = 0; u < 4; u++) xr_row(i + u * NT, pi[u], xi[u], qi[u], ri[u]);
             }
-            for (; i < r1; i += BLOCK) xr_row(i, S.p[i], S.x[i], S.q[i], S.r[i]);
+            for (; i < r1; i += NT) xr_row(i, S.p[i], S.x[i], S.q[i], S.r[i]);
         }
         __syncthreads();
-        const DotOut cn = dot(S.r, S.r, scan_r, nz2, bad2, sg2);
+        const DotOut cn = dot(S.r, S.r, scan_r, sg2);
         if (!(healthy = cn.ok)) break;
         if (cn.all_perf) {
             status = QDOT_E_BREAKDOWN;
             break;
         }
-        const double beta = cn.value / c;
+        const double beta = cn.value / rr;
         // p = r + beta p (four rows' loads in flight per thread)
         {
             int64_t i = r0 + threadIdx.x;
-            for (; i + 3 * BLOCK < r1; i += 4 * BLOCK) {
+            for (; i + 3 * NT < r1; i += 4 * NT) {
                 double pi[4], ri[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    pi[u] = S.p[i + u * BLOCK];
-                    ri[u] = S.r[i + u * BLOCK];
+                    pi[u] = S.p[i + u * NT];
+                    ri[u] = S.r[i + u * NT];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     const double bp = beta * pi[u];
-                    st_dev(&S.p[i + u * BLOCK], ri[u] + bp);
+                    st_dev(&S.p[i + u * NT], ri[u] + bp);
                 }
             }
-            for (; i < r1; i += BLOCK) {
+            for (; i < r1; i += NT) {
                 const double bp = beta * S.p[i];
                 st_dev(&S.p[i], S.r[i] + bp);
             }
         }
-        c = cn.value;
+        rr = cn.value;
         iters++;
-        if (!(sqrt(c) > thresh)) done = true;
+        if (!(sqrt(rr) > thresh)) done = true;
     }
     double relres_true = 0.0;
-    if (healthy) healthy = gang_barrier(gg, G, gb);  // x complete
+    if (healthy) healthy = gang_barrier(c);  // x complete
     if (healthy) {
-        spmv_rows(S, S.x, S.q, r0, r1);
-        for (int64_t i = r0 + threadIdx.x; i < r1; i += BLOCK) S.q[i] = S.b[i] - S.q[i];
+        load_rows<NT>(S, r0 + M.n_res, r1, R);
+        spmv_rows<NT, LE>(S, S.x, r0, r1, M, R,
+                          [&](int64_t i, double yi) { S.q[i] = S.b[i] - yi; });
         __syncthreads();
-        const DotOut rq = gang_dot64(S.q, S.q, r0, r1, gg, G, gb, k, L);
+        const DotOut rq = gang_dot64<NT>(S.q, S.q, r0, r1, c, k, L);
         k ^= 1;
         healthy = rq.ok;
         relres_true = bnorm > 0.0 ? sqrt(rq.value) / bnorm : 0.0;
@@ -820,27 +1059,41 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     if (gb == 0 && threadIdx.x == 0) {
         res->iters = iters;
         res->status = healthy ? status : QDOT_E_DEVICE;
-        res->relres_est = bnorm > 0.0 ? sqrt(c) / bnorm : 0.0;
+        res->relres_est = bnorm > 0.0 ? sqrt(rr) / bnorm : 0.0;
         res->relres_true = relres_true;
     }
     // leave the gang buffers clean and every block past its last use of them
-    if (healthy) gang_barrier(gg, G, gb);
+    if (healthy)
+        gang_barrier_then(c, [&] {
+            if ((int)threadIdx.x < c.groups) {
+                st_dev(&gg->val[0][threadIdx.x].w, NO_VALUE);
+                st_dev(&gg->val[1][threadIdx.x].w, NO_VALUE);
+            }
+        });
+    // the release is complete before this block enters the gang again
+    vmem_drain();
+    __syncthreads();
 }
 
-// Clears a gang's barrier, abort flag and histogram buffers (plain stores;
-// used by a kernel of its own, before the launch that uses the gang).
+// Clears a gang's barrier, abort flag, values and histogram buffers (plain
+// stores; used by a kernel of its own, before the launch that uses the gang).
 __device__ __forceinline__ void gang_reset(Gang *gg)
 {
-    for (int i = threadIdx.x; i < W; i += blockDim.x) {
-        for (int c = 0; c < GANG_HIST_COPIES; c++) {
-            gg->qb[0].hist[c][i] = 0u;
-            gg->qb[1].hist[c][i] = 0u;
+    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < FQ; i += blockDim.x)
+        for (int k = 0; k < 2; k++) {
+            for (int q = 0; q < BAR_GROUPS; q++) gg->qb[k].hist[q][i] = z;
+            gg->qb[k].hm[i] = z;
         }
+    if (threadIdx.x < BAR_GROUPS) {
+        gg->sub[threadIdx.x].v = 0u;
+        gg->gen[threadIdx.x].v = 0u;
+        gg->val[0][threadIdx.x].w = NO_VALUE;
+        gg->val[1][threadIdx.x].w = NO_VALUE;
     }
-    if (threadIdx.x < BAR_GROUPS) gg->bar_sub[threadIdx.x][0] = 0u;
     if (threadIdx.x == 0) {
-        gg->bar_count = 0;
-        gg->abort = 0;
+        gg->top.v = 0u;
+        gg->abort = 0u;
     }
 }
 

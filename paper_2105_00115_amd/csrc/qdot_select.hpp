@@ -49,17 +49,19 @@ struct Sel {
     int e_max, e_min, n_bins, t, c32;
     unsigned int n_zero, signs;
     int status;  // QDOT_OK, or the error that the result reports
+    int kept;    // some component is not perforated
     __device__ bool live() const { return status == QDOT_OK && n_bins > 0; }
 };
 
 template <int NT>
 struct SelLds {
     int top, bot, bins;  // highest and lowest live slot, live slots
+    int kept;            // some class is not perforated
     unsigned int cnt[NT / 64][3];
     double bound[CUT_THREADS / 64];
     int unatt[NT / 64];
     double sum;          // S of the combine (units of 2^e_max)
-    int over;            // QDOT_F_OVERFLOW of the combine
+    qdot_result sums;    // value, parts and overflow flag of the combine
 };
 
 // Before find_window, with a barrier between.
@@ -70,6 +72,7 @@ __device__ __forceinline__ void select_begin(SelLds<NT> &S)
         S.top = -1;
         S.bot = W;
         S.bins = 0;
+        S.kept = 0;
     }
 }
 
@@ -119,7 +122,7 @@ __device__ __forceinline__ int sel_class(int sigma, int nonstrict, int mu_single
 // barrier that completes h and the window; it ends with one.
 template <int NT>
 __device__ __forceinline__ Sel select_classes(const unsigned int *h, const SelArgs &a,
-                                              const SelLds<NT> &S, unsigned char *lut)
+                                              SelLds<NT> &S, unsigned char *lut)
 {
     const int tid = threadIdx.x;
     const int top = S.top, bot = S.bot;
@@ -138,11 +141,13 @@ __device__ __forceinline__ Sel select_classes(const unsigned int *h, const SelAr
 #pragma unroll 1
     for (int j = bot + tid; j <= top; j += NT) {
         const unsigned int m = h[j];
-        const int cls = sel_class(sigma_of(m, j, s), a.nonstrict, a.mu_single);
-        lut[j] = (unsigned char)(m ? cls : QDOT_PERF);
+        const int cls = m ? sel_class(sigma_of(m, j, s), a.nonstrict, a.mu_single) : QDOT_PERF;
+        lut[j] = (unsigned char)cls;
+        if (cls != QDOT_PERF) S.kept = 1;
     }
     if (tid == 0) lut[ZERO_SLOT] = (unsigned char)QDOT_PERF;
     __syncthreads();
+    s.kept = S.kept;
     return s;
 }
 
@@ -191,52 +196,63 @@ __device__ __forceinline__ void select_count(const unsigned int *h, const Sel &s
     }
 }
 
-// The whole result into R: wave 0 finishes select_count's sums (counts,
-// bounds and flags as block_cutoff forms them), wave 1 the class sums (red,
-// per wave, as block_reduce3_waves leaves them) with combine_value, both at
-// the same time.  Every thread calls it, after a barrier; it ends with one.
-// The sum before scaling is left in S.sum (0 when nothing was kept).
+// The result's fields that follow from the selection and select_count's sums,
+// as block_cutoff forms them; value and parts are those of an empty sum.  One
+// thread calls it, after a barrier.
+template <int NT>
+__device__ __forceinline__ void result_fields(const Sel &s, const SelArgs &a, int64_t n,
+                                              const SelLds<NT> &S, qdot_result &R)
+{
+    constexpr int NW = NT / 64;
+    long long c[3] = {0, 0, 0};
+    double b = 0.0;
+    int u = 0;
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        for (int q = 0; q < 3; q++) c[q] += S.cnt[w][q];
+        u |= S.unatt[w];
+    }
+#pragma unroll
+    for (int w = 0; w < CUT_THREADS / 64; w++) b += S.bound[w];
+    const bool live = s.live(), bad = s.status != QDOT_OK;
+    const bool none = c[0] + c[1] + c[2] == 0;
+    int flags = u ? QDOT_F_UNATTAINABLE : 0;
+    // Thm 3.6, as in block_cutoff
+    if ((long long)s.e_max - s.e_min <= -(long long)s.t - (a.mu_single ? 10 : 23))
+        flags |= QDOT_F_THM_ALL_DOUBLE;
+    if (none) flags |= QDOT_F_ALL_PERF;
+    // an error result: status and a NaN value, every other field 0
+    R.status = s.status;
+    R.value = bad ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
+    R.part[0] = R.part[1] = R.part[2] = 0.0;
+    R.n_zero = bad ? 0 : s.n_zero;
+    R.n_bins = live ? s.n_bins : 0;
+    R.e_max = R.e_ref = live ? s.e_max : 0;
+    R.e_min = live ? s.e_min : 0;
+    R.t = live ? s.t : 0;
+    R.count[QDOT_DOUBLE] = live ? c[0] : 0;
+    R.count[QDOT_SINGLE] = live ? c[1] : 0;
+    R.count[QDOT_HALF] = live ? c[2] : 0;
+    R.count[QDOT_PERF] = bad ? 0 : live ? n - c[0] - c[1] - c[2] : n;
+    R.bound_rel = live ? b : 0.0;
+    R.bound_abs = live ? ldexp(b, s.e_max) : 0.0;
+    R.lower = 0.0;
+    R.passes = live && !none ? 1 : 0;
+    R.flags = bad ? 0 : live ? flags : QDOT_F_ALL_PERF;
+}
+
+// The whole result into R: wave 0 forms result_fields, wave 1 the class sums
+// (red, per wave, as block_reduce3_waves leaves them) with combine_value,
+// both at the same time.  Every thread calls it, after a barrier; it ends
+// with one.  The sum before scaling is left in S.sum (0 when nothing was
+// kept).
 template <int NT>
 __device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, int64_t n,
                                               SelLds<NT> &S, Acc (*red)[NT / 64], qdot_result &R)
 {
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x;
-    if (tid == 0) {
-        long long c[3] = {0, 0, 0};
-        double b = 0.0;
-        int u = 0;
-#pragma unroll
-        for (int w = 0; w < NW; w++) {
-            for (int q = 0; q < 3; q++) c[q] += S.cnt[w][q];
-            u |= S.unatt[w];
-        }
-#pragma unroll
-        for (int w = 0; w < CUT_THREADS / 64; w++) b += S.bound[w];
-        const bool live = s.live(), bad = s.status != QDOT_OK;
-        const bool none = c[0] + c[1] + c[2] == 0;
-        int flags = u ? QDOT_F_UNATTAINABLE : 0;
-        // Thm 3.6, as in block_cutoff
-        if ((long long)s.e_max - s.e_min <= -(long long)s.t - (a.mu_single ? 10 : 23))
-            flags |= QDOT_F_THM_ALL_DOUBLE;
-        if (none) flags |= QDOT_F_ALL_PERF;
-        // an error result: status and a NaN value, every other field 0
-        R.status = s.status;
-        R.n_zero = bad ? 0 : s.n_zero;
-        R.n_bins = live ? s.n_bins : 0;
-        R.e_max = R.e_ref = live ? s.e_max : 0;
-        R.e_min = live ? s.e_min : 0;
-        R.t = live ? s.t : 0;
-        R.count[QDOT_DOUBLE] = live ? c[0] : 0;
-        R.count[QDOT_SINGLE] = live ? c[1] : 0;
-        R.count[QDOT_HALF] = live ? c[2] : 0;
-        R.count[QDOT_PERF] = bad ? 0 : live ? n - c[0] - c[1] - c[2] : n;
-        R.bound_rel = live ? b : 0.0;
-        R.bound_abs = live ? ldexp(b, s.e_max) : 0.0;
-        R.lower = 0.0;
-        R.passes = live && !none ? 1 : 0;
-        R.flags = bad ? 0 : live ? flags : QDOT_F_ALL_PERF;
-    }
+    if (tid == 0) result_fields<NT>(s, a, n, S, R);
     if (tid >> 6 == 1) {
         // one lane per class, then the three together
         const int lane = tid & 63, q = lane < 3 ? lane : 0;
@@ -247,21 +263,16 @@ __device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, in
 #pragma unroll
         for (int c = 0; c < 3; c++) f[c] = Acc{__shfl(b.s, c, 64), __shfl(b.c, c, 64)};
         if (lane == 0) {
-            qdot_result V;
-            double sum = 0.0;
-            V.value = 0.0;
-            V.part[0] = V.part[1] = V.part[2] = 0.0;
-            V.flags = 0;
-            if (s.live()) sum = combine_value(f, s.e_max, s.c32, 0, &V, a.mu_single);
-            // an error result has a NaN value
-            R.value = s.status != QDOT_OK ? __longlong_as_double(0x7ff8000000000000ll) : V.value;
-            for (int c = 0; c < 3; c++) R.part[c] = V.part[c];
-            S.sum = sum;
-            S.over = V.flags;
+            S.sum = 0.0;
+            if (s.live()) S.sum = combine_value(f, s.e_max, s.c32, 0, &S.sums, a.mu_single);
         }
     }
     __syncthreads();
-    if (tid == 0) R.flags |= S.over;
+    if (tid == 0 && s.live()) {
+        R.value = S.sums.value;
+        for (int c = 0; c < 3; c++) R.part[c] = S.sums.part[c];
+        R.flags |= S.sums.flags;
+    }
     __syncthreads();
 }
 

@@ -159,3 +159,51 @@ def test_gangs_shared_out(h, sides):
         one = h.cg(A, b, xs, 1e-8, 1e-8, 40, 1)
         assert (r["iters"], r["status"]) == (one["iters"], one["status"])
         assert float((x - xs).norm()) <= 1e-9 * float(xs.norm())
+
+
+def _shuffled_rows_csr(n, long_rows, seed):
+    """SPD, diagonally dominant: random_spd_csr plus rows of several hundred
+    entries at the places given (symmetric, so their columns grow too)."""
+    rp, col, val = workloads.random_spd_csr(n, 2, seed)
+    g = workloads.rng(seed + 1)
+    i = np.repeat(np.arange(n), np.diff(rp))
+    rows, cols, vals = [i], [col.astype(np.int64)], [val]
+    for r in long_rows:
+        c = g.choice(n, 300, replace=False)
+        c = c[c != r]
+        v = -g.uniform(1e-4, 1e-3, c.shape[0])
+        rows += [np.full(c.shape[0], r), c]
+        cols += [c, np.full(c.shape[0], r)]
+        vals += [v, v]
+    import scipy.sparse as sp
+    A = sp.coo_matrix((np.concatenate(vals), (np.concatenate(rows), np.concatenate(cols))),
+                      shape=(n, n)).tocsr()
+    A = A + sp.diags(np.asarray(abs(A).sum(axis=1)).ravel())
+    A.sort_indices()
+    return A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data
+
+
+@pytest.mark.parametrize("n,long_rows", [(1, ()), (1023, ()), (1025, (7,)), (5000, (0, 1023, 4999)),
+                                         (40000, (5, 20000, 39999)), (270000, (12, 1030))])
+@pytest.mark.parametrize("opt", [[0, 0, 0, 0, 0], [0, 0, 0, 0, 1], [0, 0, 0, 1, 0]])
+def test_cg_resident_rows(h, n, long_rows, opt):
+    """Rows in LDS, the row ahead in registers, rows after them and rows past
+    the eight gathered at once, over slices of one block up to several rows
+    per thread: the iterate of each step against the oracle's.  A step's
+    error is the tolerance's (1e-10 of each inner product) and the FP64
+    rounding's, and these systems have condition numbers near 2, so after 12
+    steps the iterates agree to far below 1e-8."""
+    import torch
+    rp, col, val = (workloads.random_spd_csr(n, 3, 5) if not long_rows
+                    else _shuffled_rows_csr(n, long_rows, 5))
+    if n == 1:
+        rp, col, val = np.array([0, 1], np.int32), np.zeros(1, np.int32), np.full(1, 3.0)
+    b = workloads.normal_vector(n, 9)
+    A = q.Csr(rp, col, val)
+    bd = torch.from_numpy(b).to("cuda:0")
+    x = torch.zeros_like(bd)
+    r = h.cg(A, bd, x, 1e-300, 1e-10, 12, 1, opt)
+    o = oracle.cg(rp, col, val, b, 1e-300, 1e-10, 12, 1, opt=opt)
+    ox = o["x"]
+    assert abs(r["iters"] - o["iters"]) <= (0 if n > 1 else 12)
+    assert np.linalg.norm(x.cpu().numpy() - ox) <= 1e-8 * np.linalg.norm(ox)
