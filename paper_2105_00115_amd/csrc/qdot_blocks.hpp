@@ -78,6 +78,8 @@ __device__ __forceinline__ void stream_strided(const T *__restrict__ x, const T 
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const int64_t i0 = base + (int64_t)u * chunk + threadIdx.x * EPT;
+            // a wave that is wholly past the end has nothing to do
+            if (i0 - (int64_t)(threadIdx.x & 63) * EPT >= n) continue;
             const int64_t left = n - i0;
             const int lim = left <= 0 ? 0 : (left >= 4 ? 4 : (int)left);
             T xv[4], yv[4];
@@ -187,7 +189,7 @@ __device__ __forceinline__ void stream_strided_ts(const T *__restrict__ x,
 // checks; the single partial group (met by one block at most) is loaded with
 // per-lane limits.  body(xv, yv, i0, lim) sees 4 consecutive components
 // i0..i0+3 of which the first `lim` are real; it is called with every lane
-// of the block active.
+// of the wave active.
 template <bool VEC, int U, int NT = BLOCK, class T, class Body>
 __device__ __forceinline__ void stream_groups(const T *__restrict__ x, const T *__restrict__ y,
                                               int64_t n, Body &&body)

@@ -6,9 +6,8 @@
 // pass on that slice.  Gang barriers separate the steps that need data from
 // other slices:
 //   before the SpMV (p complete), after a qdot's pass 1 (histogram merged),
-//   after its pass 2 (partials written),
-// five per iteration (one more for an inner product that the guaranteed
-// mode sums again; one fewer per inner product in the one-pass mode).
+// three per iteration (one more for an inner product that the guaranteed
+// mode sums again), and block 0 gathers and publishes each qdot's value.
 //
 // An iteration is a chain of latencies: each barrier costs several round
 // trips to the memory that all XCDs share (0.7 to 1 us each), so they are kept
@@ -17,9 +16,10 @@
 // groups, and poll their group's own copy of the release word.  The
 // histograms of a group are added to the gang's by the group's last block
 // while the other groups still arrive; every block then reads the merged
-// counts in one round trip, whole, and selects the classes itself.  The
-// partials are combined by the last block to arrive, which releases the
-// others with the value itself: the word they poll is the inner product.
+// counts in one round trip, whole, and selects the classes itself.  After the
+// sweep there is no barrier: block 0 polls the blocks' partials themselves and
+// combines them as they come in, and the word that the others poll is the
+// inner product.
 // Poisson 1024^2, per iteration with the two-pass qdot: 87 us with counters
 // reset at each barrier, a whole-gang merge and combine by the last block and
 // 512 blocks of 256 threads; 64 us this way; 53.7 us with the matrix's
@@ -83,8 +83,8 @@ struct Gang {
     GangLine gen[BAR_GROUPS];     // .v: the group's copy of the generation
     GangLine val[2][BAR_GROUPS];  // .w: the group's copy of dot buffer k's value
     GangQ qb[2];
-    double partials[2][MAX_GANG * 6];
-    // partials[k] combined in block order by the last block to arrive
+    double partials[2][MAX_GANG * 6];  // NO_VALUE between their uses
+    // partials[k] combined in block order by block 0
     double pfin[2][6];
     // one-pass mode: per block the live slot range, zero count and non-finite
     // flag, and the result of buffer k's qdot, published by the last block to
@@ -205,26 +205,28 @@ __device__ __forceinline__ bool gang_barrier(GangCtx &c)
     return gang_barrier_then(c, [] {});
 }
 
-// A barrier that hands out one value: work() returns it in thread 0 of the
-// last block to arrive, and the others poll for it (buffer k).  The value of
-// the other buffer, which every block has read by then, is taken back.
+// Hands out one value to the gang (buffer k): in block 0, work(ok) returns it
+// in thread 0; the others poll for it.  Block 0 publishes once every block has
+// contributed to the value, so every block is past its use of the other
+// buffer's value: block 0 has to have taken that back (gang_retract, with a
+// drain after it) before it publishes.
 template <class Work>
-__device__ __forceinline__ bool gang_publish(GangCtx &c, int k, double &value, Work &&work)
+__device__ __forceinline__ bool gang_publish(const GangCtx &c, int k, double &value, Work &&work)
 {
     __shared__ int s_ok;
     __shared__ double s_v;
     Gang *gg = c.gg;
-    const bool last = gang_arrive<false>(c, [] {});
-    if (last) {
-        const double v = work();
-        if (threadIdx.x == 0) s_v = v;
-        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k ^ 1][threadIdx.x].w, NO_VALUE);
-        vmem_drain();
+    if (c.gb == 0) {
+        bool ok = true;
+        const double v = work(ok);
+        if (threadIdx.x == 0) {
+            s_v = v;
+            s_ok = ok;
+        }
         __syncthreads();
         unsigned long long bits = (unsigned long long)__double_as_longlong(s_v);
         if (bits == NO_VALUE) bits = 0x7ff8000000000000ull;
-        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k][threadIdx.x].w, bits);
-        if (threadIdx.x == 0) s_ok = 1;
+        if ((int)threadIdx.x < c.groups && s_ok) st_dev(&gg->val[k][threadIdx.x].w, bits);
     } else if (threadIdx.x == 0) {
         unsigned long long bits = NO_VALUE;
         s_ok = gang_poll(gg, [&] {
@@ -234,10 +236,47 @@ __device__ __forceinline__ bool gang_publish(GangCtx &c, int k, double &value, W
         s_v = __longlong_as_double((long long)bits);
     }
     __syncthreads();
-    c.gen++;
     value = s_v;
     const bool ok = s_ok != 0;
     __syncthreads();
+    return ok;
+}
+
+// Block 0 takes back the value of the buffer other than k.
+__device__ __forceinline__ void gang_retract(const GangCtx &c, int k)
+{
+    if ((int)threadIdx.x < c.groups) st_dev(&c.gg->val[k ^ 1][threadIdx.x].w, NO_VALUE);
+}
+
+// The words w of a block's partials as soon as it has stored them (they hold
+// NO_VALUE before), taken back at once: the words are their own flags, so a
+// block stores them and needs no drain and no counter.  valid: the calling
+// thread has words to wait for.
+template <int NW>
+__device__ __forceinline__ bool gang_take(const GangCtx &c, unsigned long long *const (&w)[NW],
+                                          bool valid, double (&out)[NW])
+{
+    unsigned long long bits[NW];
+    bool ok = true;
+    if (valid) {
+        ok = gang_poll(c.gg, [&] {
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < NW; i++) {
+                bits[i] = ld_dev(w[i]);
+                all &= bits[i] != NO_VALUE;
+            }
+            return all;
+        });
+#pragma unroll
+        for (int i = 0; i < NW; i++) {
+            out[i] = __longlong_as_double((long long)bits[i]);
+            st_dev(w[i], NO_VALUE);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NW; i++) out[i] = 0.0;
+    }
     return ok;
 }
 
@@ -303,6 +342,8 @@ __device__ __forceinline__ Acc merge_waves(Acc (*red)[NT / 64])
 // a.b over the gang's rows by qdot (buffer k), value identical in every block.
 // With `scanned` the caller has already put its rows' keys into L.h (while
 // it produced a or b) and passes its sign bits.  L.h is zero again afterwards.
+// trace_slot: where this block writes the whole result, or NULL; with_trace:
+// some block of the gang does.
 //
 // GUARD (guard_mode 1): after the combine every block evaluates the lower
 // bound of Thm 3.4 from its copy of the counts and its class table, and
@@ -315,8 +356,8 @@ template <bool GUARD, int NT>
 __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, int64_t n,
                                             int64_t r0, int64_t r1, const SelArgs &sa,
                                             GangCtx &c, int k, CgLdsT<NT> &L,
-                                            qdot_result *trace_slot, bool scanned = false,
-                                            unsigned int sg = 0)
+                                            qdot_result *trace_slot, bool with_trace,
+                                            bool scanned = false, unsigned int sg = 0)
 {
     constexpr int U = gang_u<NT>();
     constexpr int K = (FQ + NT - 1) / NT;
@@ -387,7 +428,6 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
     __syncthreads();
     const Sel s = select_classes<NT>(L.h, sa, L.sel, L.lut);
     const int lo = s.n_bins ? s.e_min - KMIN : W, hi = s.n_bins ? s.e_max - KMIN : -1;
-    // the last block to arrive after the sweep clears the merged counts
     auto clear_counts = [&]() {
         unsigned int *gm = reinterpret_cast<unsigned int *>(Q.hm);
         for (int j = lo + tid; j <= hi; j += NT) st_dev(&gm[j], 0u);
@@ -412,18 +452,27 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
             }
         }
     };
-    // the gang's partials in block order, by the last block to arrive: the
-    // classes' sums into pfin, and the combined value in thread 0
-    auto combine = [&](int e_max, int c32, int kp) -> double {
+    // block 0: the gang's partials in block order, as they come in; the
+    // classes' sums into pfin when someone will read them, and the combined
+    // value in thread 0
+    __shared__ int s_lost;
+    auto combine = [&](int e_max, int c32, int kp, bool &ok) -> double {
+        if (tid == 0) s_lost = 0;
+        __syncthreads();
         Acc f[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-        const double *pp = gg->partials[kp];
-        for (int b = tid; b < c.G; b += NT)
+        unsigned long long *pp = reinterpret_cast<unsigned long long *>(gg->partials[kp]);
+        for (int b0 = 0; b0 < c.G; b0 += NT) {
+            const int b = b0 + tid;
+            unsigned long long *const w[6] = {&pp[b],           &pp[c.G + b],     &pp[2 * c.G + b],
+                                              &pp[3 * c.G + b], &pp[4 * c.G + b], &pp[5 * c.G + b]};
+            double d[6];
+            if (!gang_take(c, w, b < c.G, d)) s_lost = 1;
 #pragma unroll
-            for (int q = 0; q < 3; q++)
-                f[q] = acc_merge(f[q], Acc{ld_dev(&pp[(2 * q) * c.G + b]),
-                                           ld_dev(&pp[(2 * q + 1) * c.G + b])});
+            for (int q = 0; q < 3; q++) f[q] = acc_merge(f[q], Acc{d[2 * q], d[2 * q + 1]});
+        }
         block_reduce3_waves<NT, true>(f, L.red);
         __syncthreads();
+        ok = !s_lost;
         double v = 0.0;
         if (tid < 64) {
             const Acc b = merge_waves<NT>(L.red);
@@ -431,9 +480,12 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
 #pragma unroll
             for (int q = 0; q < 3; q++) t[q] = lane_acc(b, 16 * q);
             if (tid == 0) {
-                for (int q = 0; q < 3; q++) {
-                    st_dev(&gg->pfin[kp][2 * q], t[q].s);
-                    st_dev(&gg->pfin[kp][2 * q + 1], t[q].c);
+                if (GUARD || with_trace) {
+                    for (int q = 0; q < 3; q++) {
+                        st_dev(&gg->pfin[kp][2 * q], t[q].s);
+                        st_dev(&gg->pfin[kp][2 * q + 1], t[q].c);
+                    }
+                    vmem_drain();
                 }
                 combine_value(t, e_max, c32, 0, &L.sel.sums);
                 v = L.sel.sums.value;
@@ -459,18 +511,24 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
     };
     const bool swept = s.live() && s.kept;
     if (swept) {
+        // every block has passed the barrier, and so the other value
+        if (c.gb == 0) gang_retract(c, k);
         sweep(s.e_max, s.c32, k);
-        if (!gang_publish(c, k, o.value, [&] {
-                clear_counts();
-                return combine(s.e_max, s.c32, k);
-            })) {
+        if (c.gb == 0) vmem_drain();
+        if (!gang_publish(c, k, o.value,
+                          [&](bool &ok) { return combine(s.e_max, s.c32, k, ok); })) {
             o.ok = false;
             return o;
         }
+        // every block has read the merged counts; they are zero again before
+        // block 0 arrives at its next barrier
+        if (c.gb == 0) clear_counts();
     } else {
-        if (!gang_publish(c, k, o.value, [&] {
+        // nothing to sum: every block knows the value
+        o.value = s.status != QDOT_OK ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
+        if (!gang_barrier_then(c, [&] {
+                gang_retract(c, k);
                 clear_counts();
-                return s.status != QDOT_OK ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
             })) {
             o.ok = false;
             return o;
@@ -526,7 +584,9 @@ __device__ __forceinline__ DotOut gang_qdot(const double *a, const double *bv, i
                 }
                 if (!p2.skip) {
                     sweep(p2.e_max, p2.c32, k ^ 1);
-                    if (!gang_barrier_then(c, [&] { (void)combine(p2.e_max, p2.c32, k ^ 1); })) {
+                    bool ok = true;
+                    if (c.gb == 0) (void)combine(p2.e_max, p2.c32, k ^ 1, ok);
+                    if (!gang_barrier(c) || !ok) {
                         o.ok = false;
                         return o;
                     }
@@ -637,8 +697,7 @@ __device__ __forceinline__ DotOut gang_qdot_s1(const double *a, const double *bv
         st_dev(rec + 3, (int)bs);
     }
     auto finish = [&]() {
-        // the other buffer's value, as gang_publish does
-        if ((int)threadIdx.x < c.groups) st_dev(&gg->val[k ^ 1][threadIdx.x].w, NO_VALUE);
+        gang_retract(c, k);
         int lo2 = W, hi2 = -1;
         unsigned int z2 = 0, bs2 = 0;
         for (int b = threadIdx.x; b < G; b += BLOCK) {
@@ -728,10 +787,21 @@ __device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, 
     };
     const double part = block_sum((s[0] + s[1]) + (s[2] + s[3]));
     if (tid == 0) st_dev(&gg->partials[k][c.gb], part);
-    o.ok = gang_publish(c, k, o.value, [&] {
+    o.ok = gang_publish(c, k, o.value, [&](bool &ok) {
         double v = 0.0;
-        for (int b = tid; b < c.G; b += NT) v += ld_dev(&gg->partials[k][b]);
-        return block_sum(v);
+        bool mine = true;
+        for (int b0 = 0; b0 < c.G; b0 += NT) {
+            unsigned long long *const w[1] = {
+                reinterpret_cast<unsigned long long *>(&gg->partials[k][b0 + tid])};
+            double d[1];
+            mine &= gang_take(c, w, b0 + tid < c.G, d);
+            v += d[0];
+        }
+        gang_retract(c, k);
+        const double sum = block_sum(v);
+        ok = __syncthreads_and(mine) != 0;
+        vmem_drain();
+        return sum;
     });
     return o;
 }
@@ -926,7 +996,8 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
                 o = gang_qdot_s1(a, bv, n, r0, r1, S.qtol, key_mode, score_mode, nonstrict, c, k,
                                  L, *S1, tab + (size_t)k * W * S1_PIECES, ts);
             else
-                o = gang_qdot<GUARD, NT>(a, bv, n, r0, r1, sa, c, k, L, ts, scanned, sg);
+                o = gang_qdot<GUARD, NT>(a, bv, n, r0, r1, sa, c, k, L, ts, S.trace != nullptr,
+                                         scanned, sg);
             ntr++;
         } else {
             o = gang_dot64<NT>(a, bv, r0, r1, c, k, L);
@@ -1075,7 +1146,7 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     __syncthreads();
 }
 
-// Clears a gang's barrier, abort flag, values and histogram buffers (plain
+// Clears a gang's barrier, abort flag, values, partials and histogram buffers (plain
 // stores; used by a kernel of its own, before the launch that uses the gang).
 __device__ __forceinline__ void gang_reset(Gang *gg)
 {
@@ -1085,6 +1156,9 @@ __device__ __forceinline__ void gang_reset(Gang *gg)
             for (int q = 0; q < BAR_GROUPS; q++) gg->qb[k].hist[q][i] = z;
             gg->qb[k].hm[i] = z;
         }
+    for (int k = 0; k < 2; k++)
+        for (int i = threadIdx.x; i < MAX_GANG * 6; i += blockDim.x)
+            gg->partials[k][i] = __longlong_as_double((long long)NO_VALUE);
     if (threadIdx.x < BAR_GROUPS) {
         gg->sub[threadIdx.x].v = 0u;
         gg->gen[threadIdx.x].v = 0u;
