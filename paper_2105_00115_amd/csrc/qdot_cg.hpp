@@ -818,48 +818,68 @@ __device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, 
 // slice), and the first row per thread after them is loaded into registers
 // before the barrier that completes v: of the three round trips of a row
 // (bounds, entries, gathers) only the gathers are left behind the barrier.
-// Rows after those, and the entries past SNZ of long rows, take the three.
+// The rows after those are loaded a row ahead, their bounds two.  The entries
+// past SNZ of long rows take their own round trips.
 //
 // Poisson 1024^2 (256 blocks of 1024 threads, 4096 rows each, half of them
-// resident), per iteration with the two-pass qdot: 53.7 us; 64 with every
-// entry read behind the barrier (the SpMV 20.5 of them), 66 with the products
-// of coalesced entries staged through LDS.  Two rows per thread in flight
-// spilled: 69.8.
+// resident), per iteration with the two-pass qdot: 64 us with every entry
+// read behind the barrier (the SpMV 20.5 of them), 66 with the products of
+// coalesced entries staged through LDS, 53.7 with the resident rows; with the
+// gathered sums 51.4, and 50.1 with the row ahead.  Two rows per thread in
+// flight at once spilled: 69.8.
+// The batch of 24 systems (64 blocks of 256 threads for the largest, 4096
+// rows each, a fifth of them resident): 4.66 ms, with the row ahead 3.82.
 // ---------------------------------------------------------------------------
-constexpr int SR = 1;
 constexpr int SNZ = 8;
 
-struct Rows {  // SR rows of one thread
-    int beg[SR], len[SR];
-    int ci[SR][SNZ];
-    double pv[SR][SNZ];
+struct Bound {  // one row's entries
+    int beg, len;
 };
 
-// Bounds and first entries of rows base + u NT + tid below r1.
-template <int NT>
-__device__ __forceinline__ void load_rows(const CgSys &S, int64_t base, int64_t r1, Rows &R)
+struct Row {  // bounds and first entries of one row
+    Bound b;
+    int ci[SNZ];
+    double pv[SNZ];
+};
+
+// Row base + tid of the slice below r1 (empty past it).
+__device__ __forceinline__ Bound load_bound(const CgSys &S, int64_t base, int64_t r1)
 {
+    const int64_t i = base + threadIdx.x;
+    Bound b = {0, 0};
+    if (i < r1) {
+        b.beg = S.rowptr[i];
+        b.len = S.rowptr[i + 1] - b.beg;
+    }
+    return b;
+}
+
+__device__ __forceinline__ void load_entries(const CgSys &S, Bound b, Row &R)
+{
+    R.b = b;
 #pragma unroll
-    for (int u = 0; u < SR; u++) {
-        const int64_t i = base + u * NT + threadIdx.x;
-        R.beg[u] = 0;
-        R.len[u] = 0;
-        if (i < r1) {
-            R.beg[u] = S.rowptr[i];
-            R.len[u] = S.rowptr[i + 1] - R.beg[u];
+    for (int jj = 0; jj < SNZ; jj++) {
+        R.ci[jj] = 0;
+        R.pv[jj] = 0.0;
+        if (jj < b.len) {
+            R.ci[jj] = S.col[b.beg + jj];
+            R.pv[jj] = S.val[b.beg + jj];
         }
     }
-#pragma unroll
-    for (int u = 0; u < SR; u++)
-#pragma unroll
-        for (int jj = 0; jj < SNZ; jj++) {
-            R.ci[u][jj] = 0;
-            R.pv[u][jj] = 0.0;
-            if (jj < R.len[u]) {
-                R.ci[u][jj] = S.col[R.beg[u] + jj];
-                R.pv[u][jj] = S.val[R.beg[u] + jj];
-            }
-        }
+}
+
+// What a thread holds of the rows after the resident ones before the barrier
+// that completes v: the first row, and the next one's bounds.
+struct RowsAhead {
+    Row first;
+    Bound next;
+};
+
+template <int NT>
+__device__ __forceinline__ void load_ahead(const CgSys &S, int64_t base, int64_t r1, RowsAhead &R)
+{
+    load_entries(S, load_bound(S, base, r1), R.first);
+    R.next = load_bound(S, base + NT, r1);
 }
 
 // The block's resident rows in LDS.
@@ -901,71 +921,68 @@ __device__ __forceinline__ void mat_load(const CgSys &S, int64_t r0, int64_t r1,
     __syncthreads();
 }
 
-// R: load_rows of the rows after the resident ones, taken before the barrier
+// R: load_ahead of the rows after the resident ones, taken before the barrier
 // that completed v.  own(i, yi) is called once per row with its result.
 template <int NT, int LE, class Own>
 __device__ __forceinline__ void spmv_rows(const CgSys &S, const double *v, int64_t r0, int64_t r1,
-                                          const MatLds<NT, LE> &M, Rows &R, Own &&own)
+                                          const MatLds<NT, LE> &M, RowsAhead &R, Own &&own)
 {
     const int tid = threadIdx.x;
     const int n_res = M.n_res;
-    for (int base = 0; base < n_res; base += SR * NT) {
-        double g[SR][SNZ];
-        int beg[SR], len[SR];
-#pragma unroll
-        for (int u = 0; u < SR; u++) {
-            const int i = base + u * NT + tid;
-            beg[u] = 0;
-            len[u] = 0;
-            if (i < n_res) {
-                beg[u] = M.off[i];
-                len[u] = M.off[i + 1] - beg[u];
-            }
+    for (int base = 0; base < n_res; base += NT) {
+        const int i = base + tid;
+        double g[SNZ];
+        int beg = 0, len = 0;
+        if (i < n_res) {
+            beg = M.off[i];
+            len = M.off[i + 1] - beg;
         }
 #pragma unroll
-        for (int u = 0; u < SR; u++)
+        for (int jj = 0; jj < SNZ; jj++) {
+            g[jj] = 0.0;
+            if (jj < len) g[jj] = ld_dev(&v[M.col[beg + jj]]);
+        }
+        double s = 0.0;
 #pragma unroll
-            for (int jj = 0; jj < SNZ; jj++) {
-                g[u][jj] = 0.0;
-                if (jj < len[u]) g[u][jj] = ld_dev(&v[M.col[beg[u] + jj]]);
-            }
-#pragma unroll
-        for (int u = 0; u < SR; u++) {
-            double s = 0.0;
-#pragma unroll
-            for (int jj = 0; jj < SNZ; jj++)
-                if (jj < len[u]) {
-                    const double pr = M.val[beg[u] + jj] * g[u][jj];
-                    s = s + pr;
-                }
-            for (int j = beg[u] + SNZ; j < beg[u] + len[u]; j++) {
-                const double pr = M.val[j] * ld_dev(&v[M.col[j]]);
+        for (int jj = 0; jj < SNZ; jj++)
+            if (jj < len) {
+                const double pr = M.val[beg + jj] * g[jj];
                 s = s + pr;
             }
-            const int i = base + u * NT + tid;
-            if (i < n_res) own(r0 + i, s);
+        for (int j = beg + SNZ; j < beg + len; j++) {
+            const double pr = M.val[j] * ld_dev(&v[M.col[j]]);
+            s = s + pr;
         }
+        if (i < n_res) own(r0 + i, s);
     }
-    for (int64_t base = r0 + n_res; base < r1; base += SR * NT) {
-        if (base != r0 + n_res) load_rows<NT>(S, base, r1, R);
+    Row cur = R.first;
+    Bound nb = R.next;
+    for (int64_t base = r0 + n_res; base < r1; base += NT) {
+        double g[SNZ];
 #pragma unroll
-        for (int u = 0; u < SR; u++)
+        for (int jj = 0; jj < SNZ; jj++) {
+            g[jj] = 0.0;
+            if (jj < cur.b.len) g[jj] = ld_dev(&v[cur.ci[jj]]);
+        }
+        // the next row's entries, and the bounds after them, travel with the
+        // gathers
+        Row nxt;
+        load_entries(S, nb, nxt);
+        nb = load_bound(S, base + 2 * NT, r1);
+        double s = 0.0;
 #pragma unroll
-            for (int jj = 0; jj < SNZ; jj++)
-                if (jj < R.len[u]) R.pv[u][jj] = R.pv[u][jj] * ld_dev(&v[R.ci[u][jj]]);
-#pragma unroll
-        for (int u = 0; u < SR; u++) {
-            double s = 0.0;
-#pragma unroll
-            for (int jj = 0; jj < SNZ; jj++)
-                if (jj < R.len[u]) s = s + R.pv[u][jj];
-            for (int j = R.beg[u] + SNZ; j < R.beg[u] + R.len[u]; j++) {
-                const double pr = S.val[j] * ld_dev(&v[S.col[j]]);
+        for (int jj = 0; jj < SNZ; jj++)
+            if (jj < cur.b.len) {
+                const double pr = cur.pv[jj] * g[jj];
                 s = s + pr;
             }
-            const int64_t i = base + u * NT + tid;
-            if (i < r1) own(i, s);
+        for (int j = cur.b.beg + SNZ; j < cur.b.beg + cur.b.len; j++) {
+            const double pr = S.val[j] * ld_dev(&v[S.col[j]]);
+            s = s + pr;
         }
+        const int64_t i = base + tid;
+        if (i < r1) own(i, s);
+        cur = nxt;
     }
 }
 
@@ -1009,8 +1026,8 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     bool healthy = true;
     // r0 = b - A x0, p0 = r0
     mat_load<NT, LE>(S, r0, r1, M);
-    Rows R;
-    load_rows<NT>(S, r0 + M.n_res, r1, R);
+    RowsAhead R;
+    load_ahead<NT>(S, r0 + M.n_res, r1, R);
     spmv_rows<NT, LE>(S, S.x, r0, r1, M, R, [&](int64_t i, double yi) {
         const double v = S.b[i] - yi;
         S.r[i] = v;
@@ -1036,7 +1053,7 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
             status = QDOT_E_MAXIT;
             break;
         }
-        load_rows<NT>(S, r0 + M.n_res, r1, R);
+        load_ahead<NT>(S, r0 + M.n_res, r1, R);
         if (!(healthy = gang_barrier(c))) break;  // p complete
         // pass 1 of the two-pass qdot(p, q) rides in the SpMV; the one-pass
         // qdot reads its rows itself
@@ -1118,7 +1135,7 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     double relres_true = 0.0;
     if (healthy) healthy = gang_barrier(c);  // x complete
     if (healthy) {
-        load_rows<NT>(S, r0 + M.n_res, r1, R);
+        load_ahead<NT>(S, r0 + M.n_res, r1, R);
         spmv_rows<NT, LE>(S, S.x, r0, r1, M, R,
                           [&](int64_t i, double yi) { S.q[i] = S.b[i] - yi; });
         __syncthreads();
