@@ -1059,11 +1059,14 @@ __device__ __forceinline__ void put_result(qdot_result *o, const qdot_result &R)
 // holds the double class) take the float decomposition: the same single and
 // half leaves bit for bit, formed in FP32 (the float significands are exact),
 // and no double leaf.
-template <bool CLS, class T>
+// CNT: the components are also counted into the LDS histogram h when `count`
+// (zero products at FH_ZERO, non-finite ones at FH_BAD).
+template <bool CLS, bool CNT = false, class T>
 __device__ __forceinline__ void acc_group(const T *xv, const T *yv, int lim,
                                           const unsigned char *lut, int key_mode, int e_max,
                                           int c32, bool accumulate, Acc &aD, Acc &aS, Acc &aH,
-                                          unsigned char *cls_out)
+                                          unsigned char *cls_out, unsigned int *h = nullptr,
+                                          bool count = false)
 {
     float ls[4], lh[4];
     if constexpr (sizeof(T) == 4) {
@@ -1074,6 +1077,7 @@ __device__ __forceinline__ void acc_group(const T *xv, const T *yv, int lim,
         for (int e = 0; e < 4; e++) {
             const CompF c = component_f(xv[e], yv[e], key_mode);
             const bool valid = e < lim;
+            if (CNT && count && valid) atomicAdd(&h[c.slot + (c.bad ? 1 : 0)], 1u);
             const int cls = valid ? (int)lut[c.slot] : QDOT_PERF;
             if (CLS && valid)
                 cls_out[e] = (unsigned char)(cls == SINGLE_IN ? QDOT_SINGLE : cls);
@@ -1105,6 +1109,7 @@ __device__ __forceinline__ void acc_group(const T *xv, const T *yv, int lim,
     for (int e = 0; e < 4; e++) {
         const Comp c = component((double)xv[e], (double)yv[e], key_mode);
         const bool valid = e < lim;
+        if (CNT && count && valid) atomicAdd(&h[c.slot + (c.bad ? 1 : 0)], 1u);
         const int cls = valid ? (int)lut[c.slot] : QDOT_PERF;
         if (CLS && valid) cls_out[e] = (unsigned char)cls;
         double dl = ldexp(c.mp, c.es - e_max);

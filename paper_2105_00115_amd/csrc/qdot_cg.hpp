@@ -316,14 +316,6 @@ constexpr int gang_u()
     return NT >= 1024 ? 1 : 2;
 }
 
-__device__ __forceinline__ uint4 ld_dev_quad(const uint4 *p)
-{
-    const unsigned long long *w = reinterpret_cast<const unsigned long long *>(p);
-    const unsigned long long a = ld_dev(w), b = ld_dev(w + 1);
-    return make_uint4((unsigned int)a, (unsigned int)(a >> 32), (unsigned int)b,
-                      (unsigned int)(b >> 32));
-}
-
 // The waves' sums of the three classes (red, per wave) merged in the first
 // wave: lane 16 q holds class q's.  A barrier precedes it.
 template <int NT>

@@ -43,12 +43,15 @@ constexpr uint64_t ONE_BITS = 0x3ff0000000000000ull;
 // behind them, the zero products, the non-finite ones, and the waves that saw
 // a negative and a positive product, as 32-bit counts in quads of slots.
 constexpr int FH_COPIES = 4;
+constexpr int FS_COPIES = 2;                // of the sample's counts
 constexpr int FH_ZERO = W, FH_BAD = W + 1, FH_NEG = W + 2, FH_POS = W + 3;
 constexpr int FQ = (W + 4) / 4;             // quads of a histogram
 static_assert(W % 4 == 0, "the four counts behind the slots are one quad");
 constexpr int ARRIVE_GROUPS = 8;
 struct FusedWs {
     uint4 hist[FH_COPIES][FQ];               // zero between calls
+    uint4 samp[FS_COPIES][FQ];               // the same of a sample, counted ahead (follows hist)
+    int done;                                // the guessed classes stood: nothing left to sweep
     unsigned int arrive;                     // blocks (or groups) done with the sweep
     unsigned int pad[31];
     unsigned int sub[ARRIVE_GROUPS][32];     // one 128-byte line per group

@@ -83,12 +83,11 @@ struct FirstGroup {
     }
 };
 
-// The block's counts into copy blockIdx % copies of the workspace's:
-// neighbouring lanes add to neighbouring slots, so that one request carries a
-// line of them.
-__device__ __forceinline__ void merge_counts(const unsigned int *h, Ws *ws, int copies)
+// The block's counts into copy blockIdx % copies of dst: neighbouring lanes
+// add to neighbouring slots, so that one request carries a line of them.
+__device__ __forceinline__ void merge_counts(const unsigned int *h, uint4 (*dst)[FQ], int copies)
 {
-    unsigned int *gh = reinterpret_cast<unsigned int *>(ws->fused.hist[blockIdx.x % copies]);
+    unsigned int *gh = reinterpret_cast<unsigned int *>(dst[blockIdx.x % copies]);
     for (int i = threadIdx.x; i < 4 * FQ; i += BLOCK) {
         const unsigned int v = h[i];
         if (v) atomicAdd(&gh[i], v);
@@ -121,7 +120,7 @@ __global__ __launch_bounds__(BLOCK) void k_key_scan(const T *__restrict__ x,
                            });
     count_signs(sg, h);
     __syncthreads();
-    merge_counts(h, ws, copies);
+    merge_counts(h, ws->fused.hist, copies);
 }
 
 // The power method's pair: x . w into wa and w . w into wb, x and w read once.
@@ -155,8 +154,8 @@ __global__ __launch_bounds__(BLOCK) void k_key_scan_pair(const double *__restric
     count_signs(sga, ha);
     count_signs(sgb, hb);
     __syncthreads();
-    merge_counts(ha, wa, copies);
-    merge_counts(hb, wb, copies);
+    merge_counts(ha, wa->fused.hist, copies);
+    merge_counts(hb, wb->fused.hist, copies);
 }
 
 // Counts this block as done with its sweep; true in every thread of the
@@ -240,7 +239,9 @@ __device__ __forceinline__ void merge_partials(const double *partials, int nblk,
 // GUARD (guard_mode 1): the last block also certifies the result, or selects
 // the classes again and leaves them, the counts and g_redo to k_resweep.
 // ---------------------------------------------------------------------------
-template <class T, bool VEC, int U, bool GUARD>
+// SPEC: after k_spec_sweep, whose counts are split over hist and samp (all
+// copies); nothing is left to do when its guess stood.
+template <class T, bool VEC, int U, bool GUARD, bool SPEC = false>
 __device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__restrict__ y,
                                           int64_t n, const SelArgs &a, Ws *__restrict__ ws,
                                           int copies, double *__restrict__ partials,
@@ -255,17 +256,27 @@ __device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__re
     const unsigned int *h = reinterpret_cast<const unsigned int *>(h4);
     const int tid = threadIdx.x;
     FusedWs &F = ws->fused;
+    if (SPEC && F.done) return;
 
     uint4 v[K];
     {
         auto quad = [&](int c, int k) {
             const int q = k * BLOCK + tid;
-            return q < FQ ? F.hist[c][q] : make_uint4(0u, 0u, 0u, 0u);
+            return q < FQ ? F.hist[0][c * FQ + q] : make_uint4(0u, 0u, 0u, 0u);
         };
         auto plus = [](uint4 p, uint4 r) {
             return make_uint4(p.x + r.x, p.y + r.y, p.z + r.z, p.w + r.w);
         };
-        if (copies == 1) {
+        if constexpr (SPEC) {
+            static_assert(offsetof(FusedWs, samp) == FH_COPIES * FQ * sizeof(uint4),
+                          "samp follows hist");
+#pragma unroll
+            for (int k = 0; k < K; k++) v[k] = quad(0, k);
+#pragma unroll 1
+            for (int c = 1; c < (FH_COPIES + FS_COPIES); c++)
+#pragma unroll
+                for (int k = 0; k < K; k++) v[k] = plus(v[k], quad(c, k));
+        } else if (copies == 1) {
 #pragma unroll
             for (int k = 0; k < K; k++) v[k] = quad(0, k);
         } else if (copies == 2) {
@@ -312,8 +323,8 @@ __device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__re
 
     // the last block: the result, and the counts zero for the next call
     merge_partials(partials, nblk, red);
-    for (int c = 0; c < copies; c++)
-        for (int i = tid; i < FQ; i += BLOCK) F.hist[c][i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = tid; i < (SPEC ? (FH_COPIES + FS_COPIES) : copies) * FQ; i += BLOCK)
+        F.hist[0][i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     finish_result<BLOCK>(s, a, n, S, red, R);
     if constexpr (GUARD) {
@@ -378,14 +389,213 @@ __device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__re
     put_result(out, R);
 }
 
-template <class T, bool VEC, int U, bool GUARD>
+template <class T, bool VEC, int U, bool GUARD, bool SPEC = false>
 __global__ __launch_bounds__(BLOCK, GUARD ? 1 : 4) void k_sel_sweep(const T *__restrict__ x,
                                                      const T *__restrict__ y, int64_t n,
                                                      SelArgs a, Ws *__restrict__ ws, int copies,
                                                      double *__restrict__ partials,
                                                      qdot_result *__restrict__ out)
 {
-    sel_sweep<T, VEC, U, GUARD>(x, y, n, a, ws, copies, partials, out, blockIdx.x, gridDim.x);
+    sel_sweep<T, VEC, U, GUARD, SPEC>(x, y, n, a, ws, copies, partials, out, blockIdx.x, gridDim.x);
+}
+
+// ---------------------------------------------------------------------------
+// Long vectors, one pass over them where it can be: k_key_sample counts a
+// sample (one run in 2^up), every block of k_spec_sweep selects the classes from
+// the sample's counts as if they were the whole's, and reads its components
+// once, counting them and summing their leaves by the guessed classes.  The
+// last block selects from the whole counts: when every live bin has the class
+// that was guessed, the sums are those of the sweep, and it writes the result.
+// When one has not, k_sel_sweep sums again with the right classes: the counts
+// are complete, so nothing but time is lost.  The guess enters no result.
+//
+// The guess holds when the sample sees the largest exponent and no count near
+// a class boundary lies within its error of a power of two.  Where the
+// largest products are rare the sample does not see them and the sums would
+// be wasted: k_spec_sweep then only counts (guess_holds), and k_sel_sweep sums
+// as always.
+//
+// The bound is HBM: 16 bytes per component once, plus the sample again, in
+// place of twice 16.  2^27 components: 698 us with two passes, 379 where the
+// guess stands (10**U[-20, 20], family A; k_spec_sweep 356 us, 6.0 TB/s), 700
+// where it is not used (normal, family B).  5e7 floats: 168, 122 and 173.
+// Left to the blocks of one scan, which started to sum once the sample was
+// counted, it took 475 us: the guess came 25 us into the launch.
+// ---------------------------------------------------------------------------
+
+// Whether the sample's top bin is likely the whole's: the counts of its three
+// highest slots, continued by the change of their ratios, give the count that
+// the next slot would have if the tail went on.  A sample that should have
+// seen it and did not has seen the end of the range; one that could not have
+// seen it says nothing, unless the whole would not have it either.
+// The whole may also hold rare bins below the sample's, about one per doubling
+// of the counts: t has to be the same with them.
+__device__ __forceinline__ bool guess_holds(const unsigned int *h, const Sel &s,
+                                            const SelArgs &a, int up)
+{
+    if (!s.live()) return false;
+    if (a.score_mode == 0 && h[s.e_min - KMIN] < 16u &&
+        floor_log2_ratio(a.tol, (unsigned long long)(s.n_bins + up + 2)) != s.t)
+        return false;
+    const int top = s.e_max - KMIN;
+    const float c0 = (float)h[top];
+    const float c1 = top >= 1 ? (float)h[top - 1] : 0.0f;
+    const float c2 = top >= 2 ? (float)h[top - 2] : 0.0f;
+    if (c1 == 0.0f) return c0 >= 4096.0f;
+    const float r1 = c0 / c1;
+    const float next = c2 == 0.0f ? c0 * r1 * r1 : c0 * r1 * (r1 * c2 / c1);
+    return next >= 4.0f || ldexpf(next, up) < 0.02f;
+}
+
+// Runs of 4 CHUNK components; the multiples of 2^up are the sample.
+constexpr int64_t SAMPLE_RUN = 4 * CHUNK;
+
+// Counts the groups of CHUNK * U components of the runs that run(j) gives for
+// j = 0, 1, ..., below `runs`, block by block.
+template <class T, bool VEC, int U, class Run>
+__device__ __forceinline__ void count_runs(const T *__restrict__ x, const T *__restrict__ y,
+                                           int64_t n, int key_mode, unsigned int *h, Run &&run)
+{
+    constexpr unsigned int PER = 4 / U;  // groups of a run
+    const unsigned int runs = (unsigned int)((n + SAMPLE_RUN - 1) / SAMPLE_RUN);
+    const int64_t past = n + SAMPLE_RUN;  // a stride that ends the walk
+    unsigned int sg = 0;
+    for (unsigned int i = blockIdx.x;; i += gridDim.x) {
+        const unsigned int r = run(i / PER);
+        if (r >= runs) break;
+        stream_strided<VEC, U>(x, y, r * SAMPLE_RUN + (i % PER) * ((int64_t)CHUNK * U), past, n,
+                               [&](const T *xv, const T *yv, int64_t, int lim) {
+                                   count4(xv, yv, lim, key_mode, h, sg);
+                               });
+    }
+}
+
+template <class T, bool VEC>
+__global__ __launch_bounds__(BLOCK) void k_key_sample(const T *__restrict__ x,
+                                                      const T *__restrict__ y, int64_t n,
+                                                      int key_mode, Ws *__restrict__ ws, int up)
+{
+    __shared__ uint4 h4[FQ];
+    unsigned int *h = reinterpret_cast<unsigned int *>(h4);
+    for (int i = threadIdx.x; i < FQ; i += BLOCK) h4[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    count_runs<T, VEC, 4>(x, y, n, key_mode, h, [&](unsigned int j) { return j << up; });
+    __syncthreads();
+    merge_counts(h, ws->fused.samp, FS_COPIES);
+}
+
+template <class T, bool VEC, int U>
+__global__ __launch_bounds__(BLOCK, 4) void k_spec_sweep(const T *__restrict__ x,
+                                                         const T *__restrict__ y, int64_t n,
+                                                         SelArgs a, Ws *__restrict__ ws, int up,
+                                                         double *__restrict__ partials,
+                                                         qdot_result *__restrict__ out)
+{
+    constexpr int K = (FQ + BLOCK - 1) / BLOCK;
+    __shared__ uint4 h4[FQ];
+    __shared__ SelLds<BLOCK> S;
+    __shared__ unsigned int lut32[W_LUT / 4];
+    __shared__ Acc red[3][BLOCK / 64];
+    __shared__ qdot_result R;
+    __shared__ int s_miss;
+    unsigned int *h = reinterpret_cast<unsigned int *>(h4);
+    unsigned char *lut = reinterpret_cast<unsigned char *>(lut32);
+    const int tid = threadIdx.x;
+    FusedWs &F = ws->fused;
+    const uint4 z4 = make_uint4(0u, 0u, 0u, 0u);
+    auto plus = [](uint4 p, uint4 r) {
+        return make_uint4(p.x + r.x, p.y + r.y, p.z + r.z, p.w + r.w);
+    };
+    // a window of counts (v) into LDS, ready for select_classes
+    auto to_lds = [&](const uint4 (&v)[K]) {
+        select_begin(S);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; k++)
+            if (k * BLOCK + tid < FQ) h4[k * BLOCK + tid] = v[k];
+        find_window<BLOCK, K>(v, S);
+        __syncthreads();
+    };
+
+    // the guess; slots that the sample did not see are perforated
+    bool sum;
+    Sel g;
+    {
+        uint4 v[K];
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            const int q = k * BLOCK + tid;
+            v[k] = z4;
+            if (q < FQ)
+                for (int c = 0; c < FS_COPIES; c++) v[k] = plus(v[k], F.samp[c][q]);
+        }
+        for (int i = tid; i < W_LUT / 4; i += BLOCK) lut32[i] = 0x01010101u * QDOT_PERF;
+        to_lds(v);
+        g = select_classes<BLOCK>(h, a, S, lut, up);
+        sum = guess_holds(h, g, a, up);
+        __syncthreads();
+        for (int i = tid; i < FQ; i += BLOCK) h4[i] = z4;
+        __syncthreads();
+    }
+
+    if (blockIdx.x == 0 && tid == 0) F.done = 0;
+    if (!sum) {
+        // the scan's own shape (one group of doubles in flight, two of floats)
+        const unsigned int rest = (1u << up) - 1u;  // runs after each one of the sample
+        count_runs<T, VEC, sizeof(T) == 4 ? 2 : 1>(
+            x, y, n, a.key_mode, h,
+            [&](unsigned int j) { return j / rest * (rest + 1u) + j % rest + 1u; });
+        __syncthreads();
+        merge_counts(h, F.hist, FH_COPIES);
+        return;
+    }
+    const int64_t group = (int64_t)CHUNK * U;
+    const int64_t past = n + group;  // a stride that ends the walk
+    Acc acc[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    for (unsigned int i = blockIdx.x; i * group < n; i += gridDim.x) {
+        const bool count = ((i / (unsigned)(4 / U)) & ((1u << up) - 1u)) != 0u;  // not yet counted
+        stream_strided<VEC, U>(x, y, i * group, past, n,
+                               [&](const T *xv, const T *yv, int64_t, int lim) {
+                                   acc_group<false, true>(xv, yv, lim, lut, a.key_mode, g.e_max,
+                                                          g.c32, true, acc[0], acc[1], acc[2],
+                                                          nullptr, h, count);
+                               });
+    }
+    block_reduce3_waves<BLOCK, false>(acc, red);
+    __syncthreads();
+    merge_counts(h, F.hist, FH_COPIES);
+    store_partial(partials, blockIdx.x, gridDim.x, red);
+    vmem_drain();
+    __syncthreads();
+    if (!last_block(F, blockIdx.x, gridDim.x)) return;
+
+    if (tid == 0) s_miss = 0;
+    // the whole counts
+    uint4 v[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+        const int q = k * BLOCK + tid;
+        v[k] = z4;
+        if (q < FQ)
+            for (int c = 0; c < (FH_COPIES + FS_COPIES); c++) v[k] = plus(v[k], ld_dev_quad(&F.hist[0][c * FQ + q]));
+    }
+    to_lds(v);
+    __shared__ unsigned char lut2[W_LUT];
+    const Sel s = select_classes<BLOCK>(h, a, S, lut2);
+    if (s.live())
+        for (int j = s.e_min - KMIN + tid; j <= s.e_max - KMIN; j += BLOCK)
+            if (h[j] && lut2[j] != lut[j]) s_miss = 1;
+    // FP32 leaves stay far inside their range in the guess's units too
+    if (tid == 0 && (!s.live() || abs(s.c32 - g.c32) > 32 || abs(s.e_max - g.e_max) > 32))
+        s_miss = 1;
+    merge_partials(partials, gridDim.x, red);
+    select_count<BLOCK>(h, s, a, S);
+    __syncthreads();
+    if (s_miss) return;
+    for (int i = tid; i < (FH_COPIES + FS_COPIES) * FQ; i += BLOCK) F.hist[0][i] = z4;
+    finish_result<BLOCK>(s, a, n, S, red, R, g.e_max, g.c32);
+    put_result(out, R);
+    if (tid == 0) F.done = 1;
 }
 
 // The power method's pair in one grid of 2 g blocks: x . w (wa) in the first
@@ -568,6 +778,30 @@ static void launch_sel_sweep(const Launch &L, const T *x, const T *y, int64_t n,
     }
 }
 
+
+// The sample, the sweep by the guessed classes, and the scan and sweep of a
+// call whose guess was not taken or did not stand.
+template <class T, bool VEC>
+static void launch_spec(const Launch &L, const T *x, const T *y, int64_t n, const SelArgs &a,
+                        int up, qdot_result *out)
+{
+    // groups in flight: four of floats while counting too, two in the sweep,
+    // whose four would spill
+    constexpr int U = sizeof(T) == 4 ? 4 : 2;
+    const int grid = fused_grid<U>(n, L.acc_blocks);
+    hipLaunchKernelGGL((k_key_sample<T, VEC>), dim3(fused_grid<4>(n >> up, 512)), dim3(BLOCK), 0,
+                       L.stream, x, y, n, a.key_mode, L.ws, up);
+    if (L.ev) {
+        (void)hipEventRecord(L.ev[1], L.stream);
+        (void)hipEventRecord(L.ev[2], L.stream);
+    }
+    hipLaunchKernelGGL((k_spec_sweep<T, VEC, U>), dim3(grid), dim3(BLOCK), 0, L.stream, x, y, n, a,
+                       L.ws, up, L.partials, out);
+    // returns at once when the guess stood
+    hipLaunchKernelGGL((k_sel_sweep<T, VEC, 2, false, true>), dim3(grid), dim3(BLOCK), 0, L.stream,
+                       x, y, n, a, L.ws, FH_COPIES, L.partials, out);
+}
+
 template <class T, bool VEC, int U, int NT>
 static void launch_block_u(const Launch &L, const T *x, const T *y, int64_t n,
                            const SelArgs &a, int guard, qdot_result *out)
@@ -589,6 +823,18 @@ constexpr int64_t ONE_BLOCK_MAX = 4096;
 // against 22.5).
 constexpr int64_t WIDE_MAX = (int64_t)CHUNK * 512;
 
+// The sweep by guessed classes from 128 MiB per vector, where both no longer
+// fit the memory-side cache: there a guess that is not used costs what the
+// sample's launch does (2^24 normal products 97 us against 92, 2^27 700
+// against 687), and one that stands saves a pass.  A wrong one costs the sums
+// made for it (5e7 products 309 us, 172 when it stands).  The sample has at
+// least SPEC_SAMPLE components, less than twice that: the top bin of
+// 10**U[-20, 20] products then holds 91 or more.  On 24 draws each at 5e7
+// (three tolerances), 5 * 2^19 components guessed 21 rightly, 2^22 and 2^23
+// components 23, and 2^23 took 15 us more.
+constexpr int64_t SPEC_MIN_BYTES = (int64_t)1 << 27;
+constexpr int64_t SPEC_SAMPLE = (int64_t)1 << 22;
+
 template <class T, bool VEC>
 static void launch_fused_v(const Launch &L, const T *x, const T *y, int64_t n,
                            const SelArgs &a, int guard, qdot_result *out)
@@ -601,6 +847,11 @@ static void launch_fused_v(const Launch &L, const T *x, const T *y, int64_t n,
             (void)hipEventRecord(L.ev[2], L.stream);
         }
         return;
+    }
+    if (n * (int64_t)sizeof(T) >= SPEC_MIN_BYTES && !guard) {
+        int up = 2;
+        while ((n >> (up + 1)) >= SPEC_SAMPLE) up++;
+        return launch_spec<T, VEC>(L, x, y, n, a, up, out);
     }
     // longer vectors take the tuned groups in flight (twice as many for floats)
     const int f = sizeof(T) == 4 ? 2 : 1;

@@ -103,6 +103,14 @@ __device__ __forceinline__ void find_window(const uint4 (&v)[K], SelLds<NT> &S)
     }
 }
 
+__device__ __forceinline__ uint4 ld_dev_quad(const uint4 *p)
+{
+    const unsigned long long *w = reinterpret_cast<const unsigned long long *>(p);
+    const unsigned long long a = ld_dev(w), b = ld_dev(w + 1);
+    return make_uint4((unsigned int)a, (unsigned int)(a >> 32), (unsigned int)b,
+                      (unsigned int)(b >> 32));
+}
+
 __device__ __forceinline__ int sigma_of(unsigned int m, int slot, const Sel &s)
 {
     // eq. (bin-score-def) with exact bins
@@ -118,11 +126,12 @@ __device__ __forceinline__ int sel_class(int sigma, int nonstrict, int mu_single
 
 // e_max, e_min, N_bins and t from the window in S, and the classes of the
 // slots in it (perforated where empty) and of the zero slot into lut: the
-// only ones that a component can have.  Every thread calls it, after a
-// barrier that completes h and the window; it ends with one.
+// only ones that a component can have.  up: the counts are those of a sample
+// of one component in 2^up.  Every thread calls it, after a barrier that
+// completes h and the window; it ends with one.
 template <int NT>
 __device__ __forceinline__ Sel select_classes(const unsigned int *h, const SelArgs &a,
-                                              SelLds<NT> &S, unsigned char *lut)
+                                              SelLds<NT> &S, unsigned char *lut, int up = 0)
 {
     const int tid = threadIdx.x;
     const int top = S.top, bot = S.bot;
@@ -141,7 +150,8 @@ __device__ __forceinline__ Sel select_classes(const unsigned int *h, const SelAr
 #pragma unroll 1
     for (int j = bot + tid; j <= top; j += NT) {
         const unsigned int m = h[j];
-        const int cls = m ? sel_class(sigma_of(m, j, s), a.nonstrict, a.mu_single) : QDOT_PERF;
+        const int cls = m ? sel_class(sigma_of(m, j, s) + up, a.nonstrict, a.mu_single)
+                          : QDOT_PERF;
         lut[j] = (unsigned char)cls;
         if (cls != QDOT_PERF) S.kept = 1;
     }
@@ -243,12 +253,14 @@ __device__ __forceinline__ void result_fields(const Sel &s, const SelArgs &a, in
 
 // The whole result into R: wave 0 forms result_fields, wave 1 the class sums
 // (red, per wave, as block_reduce3_waves leaves them) with combine_value,
-// both at the same time.  Every thread calls it, after a barrier; it ends
-// with one.  The sum before scaling is left in S.sum (0 when nothing was
+// both at the same time.  e_sum, c32_sum: the units of the sums (2^e_max and
+// 2^c32, or those of a guess).  Every thread calls it, after a barrier; it
+// ends with one.  The sum before scaling is left in S.sum (0 when nothing was
 // kept).
 template <int NT>
 __device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, int64_t n,
-                                              SelLds<NT> &S, Acc (*red)[NT / 64], qdot_result &R)
+                                              SelLds<NT> &S, Acc (*red)[NT / 64], qdot_result &R,
+                                              int e_sum, int c32_sum)
 {
     constexpr int NW = NT / 64;
     const int tid = threadIdx.x;
@@ -264,7 +276,7 @@ __device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, in
         for (int c = 0; c < 3; c++) f[c] = Acc{__shfl(b.s, c, 64), __shfl(b.c, c, 64)};
         if (lane == 0) {
             S.sum = 0.0;
-            if (s.live()) S.sum = combine_value(f, s.e_max, s.c32, 0, &S.sums, a.mu_single);
+            if (s.live()) S.sum = combine_value(f, e_sum, c32_sum, 0, &S.sums, a.mu_single);
         }
     }
     __syncthreads();
@@ -274,6 +286,13 @@ __device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, in
         R.flags |= S.sums.flags;
     }
     __syncthreads();
+}
+
+template <int NT>
+__device__ __forceinline__ void finish_result(const Sel &s, const SelArgs &a, int64_t n,
+                                              SelLds<NT> &S, Acc (*red)[NT / 64], qdot_result &R)
+{
+    finish_result<NT>(s, a, n, S, red, R, s.e_max, s.c32);
 }
 
 // Per-wave sums of three accumulators into red (a barrier has to follow).

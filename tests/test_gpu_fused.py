@@ -207,3 +207,64 @@ def test_cg_resident_rows(h, n, long_rows, opt):
     ox = o["x"]
     assert abs(r["iters"] - o["iters"]) <= (0 if n > 1 else 12)
     assert np.linalg.norm(x.cpu().numpy() - ox) <= 1e-8 * np.linalg.norm(ox)
+
+
+def _long_pair(n, law, seed):
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    if law == "loguniform":
+        return workloads.log_uniform_pair_torch(n, seed)
+    if law == "familyA":
+        return workloads.paper_dist_torch(n, 13, seed, "A")
+    x = torch.randn(n, generator=g, dtype=torch.float64, device="cuda:0")
+    y = torch.randn(n, generator=g, dtype=torch.float64, device="cuda:0")
+    if law == "late":  # its second half 40 binades up: a sample's tail looks ended, but is not
+        x[n // 2 + 12345:n // 2 + 12500] *= 2.0 ** 40
+    if law == "sample only":  # the largest products lie in the sample's runs alone
+        x.view(-1)[:4096] *= 2.0 ** 40
+    if law == "constant":
+        return torch.ones_like(x), torch.full_like(x, 1.5)
+    if law == "zeros":
+        x.zero_()
+    if law == "inf":
+        x[n - 1] = float("inf")
+    return x, y
+
+
+@pytest.mark.parametrize("n,off", [(1 << 24, 0), ((1 << 24) + 1, 0), ((1 << 24) + 4097, 1),
+                                   (31_000_003, 0), ((1 << 25) - 5, 0)])
+@pytest.mark.parametrize("law", ["loguniform", "familyA", "normal", "late", "sample only",
+                                 "constant", "zeros", "inf"])
+def test_long_vectors_by_guess(h, n, off, law):
+    """Sums by guessed classes: guesses that stand, that are not used, and that
+    are wrong (the sample never sees the largest exponents), against the
+    four-kernel chain: every integer field, and the value up to the FP64
+    sums' error terms (2 units in the last place of sum |x_i y_i|)."""
+    import torch
+    x, y = _long_pair(n + off, law, 11)
+    x, y = x[off:], y[off:]
+    scale = float((x * y).abs().sum()) if law != "inf" else 1.0
+    with q.Qdot(0) as other:
+        other.set_tune(-1, 2, 1, 2, 1, block_threads=128)
+        for tol, opt in ((1e-3, None), (1e-6, None), (1e-10, [1, 1, 1, 0])):
+            c = other.qdot(x, y, tol, opt)
+            for r in (h.qdot(x, y, tol, opt), h.qdot(x, y, tol, opt)):
+                for k in FIELDS:
+                    assert r[k] == c[k], (law, tol, k, r[k], c[k])
+                assert r["bound_rel"] == c["bound_rel"]
+                if law == "inf":
+                    assert np.isnan(r["value"])
+                else:
+                    assert abs(r["value"] - c["value"]) <= 4.5e-16 * scale
+        if law in ("loguniform", "normal", "late"):
+            xf, yf = torch.cat([x, x])[:1 << 25].float(), torch.cat([y, y])[:1 << 25].float()
+            xf, yf = torch.cat([xf, xf[:3000]]), torch.cat([yf, yf[:3000]])
+            c = other.qdot_f32(xf, yf, 1e-6)
+            # the chain's float grouping is this path's own (the threads knob is
+            # for doubles), so only the routes differ
+            for r in (h.qdot_f32(xf, yf, 1e-6), h.qdot_f32(xf, yf, 1e-6)):
+                for k in FIELDS:
+                    assert r[k] == c[k], (law, k, r[k], c[k])
+                assert abs(r["value"] - c["value"]) <= 4.5e-16 * float(
+                    (xf.double() * yf.double()).abs().sum())
