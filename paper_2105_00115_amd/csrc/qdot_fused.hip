@@ -935,6 +935,12 @@ bool fused_ok(const Launch &L, int64_t n, const qdot_options &o)
            (!L.tiles || n <= WIDE_MAX) && L.acc_form == 0 && L.block_threads == BLOCK;
 }
 
+bool fused_stores_once(int64_t n, const qdot_options &o)
+{
+    // k_resweep reads the result that it completes
+    return !o.guard_mode || n <= ONE_BLOCK_MAX;
+}
+
 hipError_t launch_fused(const Launch &L, const double *x, const double *y, int64_t n, double tol,
                         const qdot_options &o, qdot_result *out)
 {

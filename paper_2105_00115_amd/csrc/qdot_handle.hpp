@@ -16,6 +16,7 @@ struct qdot_handle {
     double *s1tab = nullptr;         // one-pass mode per-bin sums (kept zero between calls)
     qdot_result *dev_res = nullptr;  // device result slot for the sync API
     qdot_result *host_res = nullptr; // pinned host mirror
+    qdot_result *host_res_dev = nullptr; // its device address
     qdot_tune tune[QDOT_TUNE_BUCKETS];
     std::string err;
 

@@ -63,6 +63,10 @@ hipError_t launch_fused(const Launch &L, const double *x, const double *y, int64
 hipError_t launch_fused(const Launch &L, const float *x, const float *y, int64_t n, double tol,
                         const qdot_options &o, qdot_result *out);
 
+// Whether launch_fused stores the result once, whole, and reads none of it: it
+// may then lie in host memory.
+bool fused_stores_once(int64_t n, const qdot_options &o);
+
 // The power method's pair of launch_qdot_pair likewise.
 hipError_t launch_fused_pair(const Launch &La, const Launch &Lb, const double *x,
                              const double *w, int64_t n, double tol, const qdot_options &o,

@@ -268,3 +268,26 @@ def test_long_vectors_by_guess(h, n, off, law):
                     assert r[k] == c[k], (law, k, r[k], c[k])
                 assert abs(r["value"] - c["value"]) <= 4.5e-16 * float(
                     (xf.double() * yf.double()).abs().sum())
+
+
+@pytest.mark.parametrize("n", [0, 3, 1000, 4096, 4097, 100001, (1 << 24) + 5])
+@pytest.mark.parametrize("dtype,opt", [(np.float64, [0, 0, 0, 0, 0]), (np.float64, [0, 0, 0, 0, 1]),
+                                       (np.float64, [0, 0, 0, 1, 0]), (np.float32, [0, 0, 0, 0, 0])])
+def test_synchronous_result_is_the_asynchronous_one(h, n, dtype, opt):
+    """The synchronous call's result, which some paths store into host memory
+    and others have copied there, is the asynchronous call's, byte for byte:
+    also after a result of another length, and of an error."""
+    import torch
+    *_, xd, yd = _pair(n, 5 + n, dtype, 0)
+    f64 = dtype == np.float64
+    sync, enqueue = (h.qdot, h.qdot_async) if f64 else (h.qdot_f32, h.qdot_f32_async)
+    bad = xd.clone()
+    if n:
+        bad[n // 2] = float("nan")
+    out = torch.zeros(q.RESULT_BYTES, dtype=torch.uint8, device="cuda:0")
+    for v in (xd, bad, xd):
+        enqueue(v, yd, 1e-5, out, opt)
+        torch.cuda.synchronize()
+        want = q.QdotResult.from_buffer_copy(out.cpu().numpy().tobytes()).as_dict()
+        r = sync(v, yd, 1e-5, opt)
+        assert repr(r) == repr(want)
