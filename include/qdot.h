@@ -308,7 +308,10 @@ QDOT_API int32_t qdot_load_tune(qdot_handle *h, const char *path);
  * launches (not allowed while the stream is being captured into a graph).
  * qdot_timing_read synchronises the recorded events and returns the summed
  * durations in milliseconds of the scan, cutoff, accumulate and finalize
- * kernels of qdot (ms[0..3]; with guard_mode 1, ms[3] also covers the guard
+ * kernels of qdot (ms[0..3]; where the sweep selects the classes and writes
+ * the result itself, ms[1] and ms[3] hold no kernel of that work, and for long
+ * vectors ms[0] is the sample and ms[2] the sweep that counts and sums; with
+ * guard_mode 1, ms[3] also covers the guard
  * stages and the second sweep; in the one-pass mode ms[1] is the single
  * cutoff-and-pick kernel and ms[2], ms[3] are 0) and of the FP64 dot (ms[4], both of its kernels), the number
  * of qdot and FP64-dot calls timed (calls[0..1]), then clears the record. */

@@ -22,8 +22,9 @@
 // inner product.
 // Poisson 1024^2, per iteration with the two-pass qdot: 87 us with counters
 // reset at each barrier, a whole-gang merge and combine by the last block and
-// 512 blocks of 256 threads; 64 us this way; 53.7 us with the matrix's
-// resident rows (below).  With the FP64 dot: 48 -> 32.8 us.
+// 512 blocks of 256 threads; 64 us with the barriers above; 53.7 us with the
+// matrix's resident rows, 51.4 with block 0 polling the sums, 50.1 with each
+// thread's next row ahead (all below).  With the FP64 dot: 48 -> 32.8 us.
 // Every block holds bit-identical scalars (alpha, beta, c) and takes the same
 // branches: no decision is broadcast.  Two buffers alternate between
 // consecutive qdots.

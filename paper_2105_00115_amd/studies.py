@@ -13,8 +13,11 @@ n = 1e5, 1e6, 1e7, 1e8.  Per cell, relerr mean / min / max and the class
 mix.  HIP-event kernel times give the approximation speedup
 t(FP64 dot) / t(computation phase) and the approximation efficiency
 t(FP64 dot) / (t(parameter selection) + t(FP64 dot)) (definitions of Sec. 2).
-The computation phase is k_acc + k_fin; the parameter selection is k_scan +
-k_cut.
+The parameter selection is the kernels before the sweep that sums, the
+computation phase that sweep and what follows it.  Below 2^24 doubles these
+are k_key_scan (the counts) and k_sel_sweep (whose blocks select the classes
+before they sum); beyond, the sample and the sweep that also counts, so the
+selection is then mostly inside the computation phase.
 
 Inputs are drawn on the device (``workloads.paper_dist_torch``), one seed per
 pair.  Every call goes through the C ABI; this module only drives it and
