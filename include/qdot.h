@@ -542,7 +542,8 @@ QDOT_API int32_t qdot_spmv_async(qdot_handle *h, const qdot_csr *A, const double
  * iterations.  trace: NULL or device qdot_result[2*maxit + 1] receiving
  * every qdot result in call order.  Synchronous; out (host) receives the
  * iteration count, status and residuals.  Returns out->status.
- * The whole solve is one persistent launch of up to two blocks per CU
+ * The whole solve is one persistent launch of one block per CU, or with
+ * accum_mode 1 or guard_mode 1 up to two smaller ones
  * (as many as can be resident together; at most 512, at least 1024 rows
  * per block; environment variable QDOT_CG_BLOCKS caps the count).  A gang
  * barrier that does not complete within its spin limit ends the solve with
