@@ -480,6 +480,9 @@ __global__ __launch_bounds__(BLOCK) void k_key_sample(const T *__restrict__ x,
 {
     __shared__ uint4 h4[FQ];
     unsigned int *h = reinterpret_cast<unsigned int *>(h4);
+    // the last block of k_spec_sweep alone sets it: two blocks of one launch
+    // must not store the same word, as their L2s write back in any order
+    if (blockIdx.x == 0 && threadIdx.x == 0) ws->fused.done = 0;
     for (int i = threadIdx.x; i < FQ; i += BLOCK) h4[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     count_runs<T, VEC, 4>(x, y, n, key_mode, h, [&](unsigned int j) { return j << up; });
@@ -541,7 +544,6 @@ __global__ __launch_bounds__(BLOCK, 4) void k_spec_sweep(const T *__restrict__ x
         __syncthreads();
     }
 
-    if (blockIdx.x == 0 && tid == 0) F.done = 0;
     if (!sum) {
         // the scan's own shape (one group of doubles in flight, two of floats)
         const unsigned int rest = (1u << up) - 1u;  // runs after each one of the sample

@@ -1,0 +1,41 @@
+"""Words of device memory that several blocks of one launch use: which stores
+the kernels may make to them, checked on the sources (a wrong order shows
+neither on the CPU nor, reliably, on the GPU)."""
+import os
+import re
+
+import pytest
+
+import paper_2105_00115_amd as q
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(q.__file__)), "csrc")
+
+
+def _body(name, file):
+    """The function or kernel `name`: from its parameter list to the brace
+    that closes it, without comments."""
+    text = open(os.path.join(CSRC, file)).read()
+    text = re.sub(r"//[^\n]*", "", text)
+    m = re.search(r"\b%s\(" % name, text)
+    assert m, name
+    i = text.index("{", text.index(")", m.end()))
+    depth, j = 0, i
+    while True:
+        depth += {"{": 1, "}": -1}.get(text[j], 0)
+        j += 1
+        if depth == 0:
+            return text[i:j]
+
+
+def test_one_block_of_a_launch_stores_the_guess_verdict():
+    """The verdict that k_sel_sweep reads is set in k_spec_sweep by the last
+    block to finish and by no other block (each XCD writes its L2 back when it
+    likes, so a plain store of another block could land after it), and cleared
+    in the launch before."""
+    store = re.compile(r"\bdone\s*=[^=]")
+    sweep = _body("k_spec_sweep", "qdot_fused.hip")
+    stores = [m.start() for m in store.finditer(sweep)]
+    assert len(stores) == 1
+    assert stores[0] > sweep.index("if (!last_block(")
+    assert len(store.findall(_body("k_key_sample", "qdot_fused.hip"))) == 1
+    assert not store.search(_body("sel_sweep", "qdot_fused.hip"))
