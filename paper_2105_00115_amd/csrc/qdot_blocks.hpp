@@ -380,7 +380,7 @@ __device__ __forceinline__ int floor_log2_ratio(double eps, unsigned long long n
     return s.e + 1 - b - (Np > S ? 1 : 0);
 }
 
-__device__ __forceinline__ int class_of(int sigma, int nonstrict)
+__host__ __device__ __forceinline__ int class_of(int sigma, int nonstrict)
 {
     // eq. (precision-def) with m_half = 10, m_single = 23; the non-strict
     // reading moves every boundary up by one (score <= m qualifies).

@@ -32,6 +32,7 @@
 // their error terms at most.
 #include "qdot_kernels.hpp"
 
+#include "qdot_guess.hpp"
 #include "qdot_select.hpp"
 
 namespace qd {
@@ -409,45 +410,68 @@ __global__ __launch_bounds__(BLOCK, GUARD ? 1 : 4) void k_sel_sweep(const T *__r
 // When one has not, k_sel_sweep sums again with the right classes: the counts
 // are complete, so nothing but time is lost.  The guess enters no result.
 //
-// The guess holds when the sample sees the largest exponent and no count near
-// a class boundary lies within its error of a power of two.  Where the
-// largest products are rare the sample does not see them and the sums would
-// be wasted: k_spec_sweep then only counts (guess_holds), and k_sel_sweep sums
-// as always.
+// The guess stands when the sample sees the largest exponent and no count
+// near a class boundary lies within its error of a power of two.  Where that
+// is not likely (guess_holds) k_spec_sweep only counts, and k_sel_sweep sums as
+// always.
 //
 // The bound is HBM: 16 bytes per component once, plus the sample again, in
-// place of twice 16.  2^27 components: 698 us with two passes, 379 where the
-// guess stands (10**U[-20, 20], family A; k_spec_sweep 356 us, 6.0 TB/s), 700
-// where it is not used (normal, family B).  5e7 floats: 168, 122 and 173.
+// place of twice 16.  2^27 components: 699 us with two passes, 381 where the
+// guess stands (10**U[-20, 20], family A), 700 where it is not used (normal,
+// uniform, family B).  5e7 floats: 168, 121 and 170.
 // Left to the blocks of one scan, which started to sum once the sample was
 // counted, it took 475 us: the guess came 25 us into the launch.
 // ---------------------------------------------------------------------------
 
-// Whether the sample's top bin is likely the whole's: the counts of its three
-// highest slots, continued by the change of their ratios, give the count that
-// the next slot would have if the tail went on.  A sample that should have
-// seen it and did not has seen the end of the range, if the counts are large
-// enough for their ratios to mean something (at the end of a normal tail they
-// are not: 1.7e7 products of family B summed for nothing took 117 us, 102 with
-// the guess left); one that could not have seen it says nothing, unless the
-// whole would not have it either.
-// The whole may also hold rare bins below the sample's, about one per doubling
-// of the counts: t has to be the same with them.
+// Words of guess_holds in LDS: `dense` W and the others zero before it, with
+// a barrier between.
+struct GuessLds {
+    int dense;  // the lowest slot that the sample saw GUESS_SEEN times
+    int empty;  // empty slots of the window below it
+    int risk;   // sum of slot_risk
+};
+
+// Whether to sum by the classes that the sample's counts h (scaled by 2^up)
+// select (s, from them): top_holds, t is the same with the rare bins that the
+// sample did not see, and the slots' risks sum to GUESS_RISK at most.  Every
+// thread of the block calls it, after a barrier, and gets the same answer,
+// which is the same in every block: the risks are whole numbers.
 __device__ __forceinline__ bool guess_holds(const unsigned int *h, const Sel &s,
-                                            const SelArgs &a, int up)
+                                            const SelArgs &a, int up, GuessLds &G)
 {
     if (!s.live()) return false;
-    if (a.score_mode == 0 && h[s.e_min - KMIN] < 16u &&
-        floor_log2_ratio(a.tol, (unsigned long long)(s.n_bins + up + 2)) != s.t)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int bot = s.e_min - KMIN, top = s.e_max - KMIN;
+    if (!top_holds(h, top, up)) return false;
+    int dense = W;
+#pragma unroll 1
+    for (int j = bot + tid; j <= top && dense == W; j += BLOCK)
+        if (h[j] >= GUESS_SEEN) dense = j;
+    dense = wave_reduce_i(dense, [](int p, int r) { return min(p, r); });
+    if (lane == 0) atomicMin(&G.dense, dense);
+    __syncthreads();
+    dense = G.dense;
+    int empty = 0, risk = 0;
+#pragma unroll 1
+    for (int j = bot - 1 + tid; j <= top; j += BLOCK) {
+        const unsigned int m = j < bot ? 0u : h[j];
+        if (m == 0u && !(j < dense && bot < dense)) continue;
+        empty += m == 0u && j >= bot;
+        const int base = j + KMIN - s.e_max - s.t + 1;  // the score of a count of 1
+        risk += slot_risk(m, sigma_of(m, j, s) - base, base + up, a.nonstrict, a.mu_single);
+    }
+    auto add = [](int p, int r) { return p + r; };
+    empty = wave_reduce_i(empty, add);
+    risk = wave_reduce_i(risk, add);
+    if (lane == 0) {
+        atomicAdd(&G.empty, empty);
+        atomicAdd(&G.risk, risk);
+    }
+    __syncthreads();
+    if (a.score_mode == 0 && bot < dense &&
+        floor_log2_ratio(a.tol, (unsigned long long)(s.n_bins + G.empty + up + 2)) != s.t)
         return false;
-    const int top = s.e_max - KMIN;
-    const float c0 = (float)h[top];
-    const float c1 = top >= 1 ? (float)h[top - 1] : 0.0f;
-    const float c2 = top >= 2 ? (float)h[top - 2] : 0.0f;
-    if (c1 == 0.0f) return c0 >= 4096.0f;
-    const float r1 = c0 / c1;
-    const float next = c2 == 0.0f ? c0 * r1 * r1 : c0 * r1 * (r1 * c2 / c1);
-    return (next >= 4.0f && c0 >= 32.0f) || ldexpf(next, up) < 0.02f;
+    return G.risk <= GUESS_RISK;
 }
 
 // Runs of 4 CHUNK components; the multiples of 2^up are the sample.
@@ -504,6 +528,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_spec_sweep(const T *__restrict__ x
     __shared__ Acc red[3][BLOCK / 64];
     __shared__ qdot_result R;
     __shared__ int s_miss;
+    __shared__ GuessLds G;
     unsigned int *h = reinterpret_cast<unsigned int *>(h4);
     unsigned char *lut = reinterpret_cast<unsigned char *>(lut32);
     const int tid = threadIdx.x;
@@ -536,9 +561,10 @@ __global__ __launch_bounds__(BLOCK, 4) void k_spec_sweep(const T *__restrict__ x
                 for (int c = 0; c < FS_COPIES; c++) v[k] = plus(v[k], F.samp[c][q]);
         }
         for (int i = tid; i < W_LUT / 4; i += BLOCK) lut32[i] = 0x01010101u * QDOT_PERF;
+        if (tid == 0) G = GuessLds{W, 0, 0};
         to_lds(v);
         g = select_classes<BLOCK>(h, a, S, lut, up);
-        sum = guess_holds(h, g, a, up);
+        sum = guess_holds(h, g, a, up, G);
         __syncthreads();
         for (int i = tid; i < FQ; i += BLOCK) h4[i] = z4;
         __syncthreads();
