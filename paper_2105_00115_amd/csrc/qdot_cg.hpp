@@ -790,9 +790,11 @@ __device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, 
             mine &= gang_take(c, w, b0 + tid < c.G, d);
             v += d[0];
         }
+        // a wave's own blocks having contributed says nothing about the others':
+        // the other value goes once every wave has its blocks' sums
+        ok = __syncthreads_and(mine) != 0;
         gang_retract(c, k);
         const double sum = block_sum(v);
-        ok = __syncthreads_and(mine) != 0;
         vmem_drain();
         return sum;
     });

@@ -42,3 +42,46 @@ def test_guess_verdicts_do_not_outlive_their_call(h):
         assert r["value"] != 0.0
     for row in res[1:]:
         assert np.array_equal(row, res[0])
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 63, 64, 65, 128, 129, 256])
+def test_fp64_dots_in_a_row(h, blocks):
+    """CG with the FP64 dot, whose inner products follow one another without a
+    barrier between, in gangs around the 64 blocks that one wave of block 0
+    waits for: the oracle's iteration count and solution.  Each step's error is
+    FP64 rounding times a condition number below 20, so the iterates
+    agree to far below 1e-9."""
+    import torch
+    n = 1024 * blocks - 3
+    rp, col, val = workloads.random_spd_csr(n, 3, 5)
+    A = q.Csr(rp, col, val)
+    b = workloads.normal_vector(n, 9)
+    o = oracle.cg(rp, col, val, b, 1e-9, 1e-10, 40, 0)
+    bd = torch.from_numpy(b).to("cuda:0")
+    for _ in range(3):
+        x = torch.zeros_like(bd)
+        r = h.cg(A, bd, x, 1e-9, 1e-10, 40, 0)
+        assert (r["status"], r["iters"]) == (o["status"], o["iters"])
+        assert np.linalg.norm(x.cpu().numpy() - o["x"]) <= 1e-9 * np.linalg.norm(o["x"])
+
+
+@pytest.mark.parametrize("gang_max", [64, 65, 200])
+def test_fp64_dots_in_a_row_batched(gang_max):
+    """The same in the batched launch, whose blocks have 256 threads."""
+    import torch
+    with q.Qdot(0) as hh:
+        hh.set_solver_tune(cg_rows_per_block=1024, cg_gang_max=gang_max)
+        systems, want = [], []
+        for m in (gang_max, 3):
+            n = 1024 * m - 5
+            rp, col, val = workloads.random_spd_csr(n, 3, 7)
+            b = workloads.normal_vector(n, 3)
+            bd = torch.from_numpy(b).to("cuda:0")
+            systems.append((q.Csr(rp, col, val), bd, torch.zeros_like(bd), 1e-9, 1e-10, 40, 0))
+            want.append(oracle.cg(rp, col, val, b, 1e-9, 1e-10, 40, 0))
+        for _ in range(3):
+            for s in systems:
+                s[2].zero_()
+            for (_, _, x, *_), r, o in zip(systems, hh.cg_batched(systems), want):
+                assert (r["status"], r["iters"]) == (o["status"], o["iters"])
+                assert np.linalg.norm(x.cpu().numpy() - o["x"]) <= 1e-9 * np.linalg.norm(o["x"])

@@ -39,3 +39,24 @@ def test_one_block_of_a_launch_stores_the_guess_verdict():
     assert stores[0] > sweep.index("if (!last_block(")
     assert len(store.findall(_body("k_key_sample", "qdot_fused.hip"))) == 1
     assert not store.search(_body("sel_sweep", "qdot_fused.hip"))
+
+
+def test_fp64_gang_dot_waits_for_every_block_before_it_takes_a_value_back():
+    """Block 0 of a gang takes back the previous inner product's value once
+    every block has contributed to this one (they have all read it then).  Its
+    waves wait for 64 blocks each, so a barrier has to stand between the waits
+    and the store: without it, wave 0 takes the value back while a block past
+    the 64th may still poll for it, and the gang waits until it gives up."""
+    body = _body("gang_dot64", "qdot_cg.hpp")
+    wait, retract = body.index("gang_take("), body.index("gang_retract(")
+    assert wait < retract
+    assert re.search(r"__syncthreads(_and)?\(", body[wait:retract])
+    # and the store is complete before the new value can be seen
+    assert "vmem_drain()" in body[retract:]
+
+
+def test_gang_qdot_takes_a_value_back_behind_a_barrier_of_the_gang():
+    """The same order in the two-pass inner product: behind its counting
+    barrier, which no block passes before it has read the other value."""
+    body = _body("gang_qdot", "qdot_cg.hpp")
+    assert body.index("gang_barrier_with<true>(") < body.index("gang_retract(")
