@@ -270,7 +270,9 @@ typedef struct qdot_tune {
 typedef struct qdot_handle qdot_handle;
 
 /* Create a handle on `device` (HIP ordinal): allocates the workspace
- * (histogram, class table, per-block partials) once.
+ * (histogram, class table, per-block partials) once.  Environment variable
+ * QDOT_SPIN_LIMIT lowers the polls after which a CG gang of the handle gives
+ * up a wait (2^26 by default): for tests of that path.
  * Returns QDOT_E_INVAL (h NULL or bad ordinal), QDOT_E_DEVICE, QDOT_E_NOMEM. */
 QDOT_API int32_t qdot_create(qdot_handle **h, int32_t device);
 

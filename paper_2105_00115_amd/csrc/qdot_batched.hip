@@ -357,17 +357,20 @@ __global__ __launch_bounds__(BLOCK) void k_batch_init(BLarge *large, int n_large
     for (int s = W; s < W_LUT; s++) lut[(size_t)i * W_LUT + s] = (unsigned char)QDOT_PERF;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_batch_gangs_init(Gang *gangs, int S)
+__global__ __launch_bounds__(BLOCK) void k_batch_gangs_init(Gang *gangs, int S,
+                                                            unsigned int spin_limit)
 {
     if (blockIdx.x >= (unsigned)S) return;
-    gang_reset(gangs + blockIdx.x);
+    gang_reset(gangs + blockIdx.x, spin_limit);
 }
 
 // Re-arms the gangs of a plan whose previous launch aborted (a bounded wait
 // ran out); a clean gang leaves its state ready for the next launch.
-__global__ __launch_bounds__(BLOCK) void k_gang_rearm(Gang *gangs, int S)
+__global__ __launch_bounds__(BLOCK) void k_gang_rearm(Gang *gangs, int S,
+                                                      unsigned int spin_limit)
 {
-    if (blockIdx.x < (unsigned)S && gangs[blockIdx.x].abort) gang_reset(gangs + blockIdx.x);
+    if (blockIdx.x < (unsigned)S && gangs[blockIdx.x].abort)
+        gang_reset(gangs + blockIdx.x, spin_limit);
 }
 
 // GUARD: guard_mode 1 for the qdot instances (two-pass) and the CG systems.
@@ -905,7 +908,8 @@ static int32_t build_plan(qdot_handle *h, const int64_t *host_offsets, int32_t B
         e = hipGetLastError();
     }
     if (e == hipSuccess && S > 0) {
-        hipLaunchKernelGGL(k_batch_gangs_init, dim3((unsigned)S), dim3(BLOCK), 0, 0, p->gangs, S);
+        hipLaunchKernelGGL(k_batch_gangs_init, dim3((unsigned)S), dim3(BLOCK), 0, 0, p->gangs, S,
+                           h->spin_limit);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1068,7 +1072,9 @@ static int32_t batch_launch(qdot_handle *h, const double *x_cat, const double *y
             return fail(h, QDOT_E_DEVICE, "CG gang larger than the resident blocks");
     }
     hipStream_t s = (hipStream_t)stream;
-    if (S > 0) hipLaunchKernelGGL(k_gang_rearm, dim3((unsigned)S), dim3(BLOCK), 0, s, p->gangs, S);
+    if (S > 0)
+        hipLaunchKernelGGL(k_gang_rearm, dim3((unsigned)S), dim3(BLOCK), 0, s, p->gangs, S,
+                           h->spin_limit);
     (void)batch_kernel(o.guard_mode != 0, cg, accum, a, grid, s, nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "batched launch");

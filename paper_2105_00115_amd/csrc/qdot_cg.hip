@@ -53,11 +53,11 @@ __global__ __launch_bounds__(NT, NT > BLOCK ? 4 : 2) void k_cg_gangs(const CgSys
     }
 }
 
-__global__ void k_gang_init(Gang *gangs, int n)
+__global__ void k_gang_init(Gang *gangs, int n, unsigned int spin_limit)
 {
     const int g = blockIdx.x;
     if (g >= n) return;
-    gang_reset(gangs + g);
+    gang_reset(gangs + g, spin_limit);
 }
 
 // ---------------------------------------------------------------------------
@@ -195,7 +195,8 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
         e = hipMemsetAsync(d->s1tab, 0, sizeof(double) * CG_S1TAB, s);
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_gang_init, dim3(1), dim3(BLOCK), 0, s, d->gangs, 1);
+        hipLaunchKernelGGL(k_gang_init, dim3(1), dim3(BLOCK), 0, s, d->gangs, 1,
+                           h->spin_limit);
         if (acc1)
             hipLaunchKernelGGL((k_cg_gangs<false, true, BLOCK>), dim3(G), dim3(BLOCK), 0, s,
                                d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,

@@ -31,7 +31,8 @@
 //
 // Every wait is bounded: a barrier that does not complete within the spin
 // limit raises the gang's abort flag, every block leaves, and the call
-// reports QDOT_E_DEVICE.  The launches size their grids so that all blocks
+// reports QDOT_E_DEVICE.  A block leaves its LDS as the next item of its
+// launch expects it.  The launches size their grids so that all blocks
 // of a gang are resident together.
 #pragma once
 #include <cmath>
@@ -39,8 +40,6 @@
 #include "qdot_select.hpp"
 
 namespace qd {
-
-constexpr unsigned SPIN_LIMIT = 1u << 26;
 
 struct CgSys {
     int64_t n;
@@ -78,7 +77,8 @@ constexpr unsigned long long NO_VALUE = 0x7ff4dead00c0ffeeull;
 
 struct Gang {
     unsigned int abort;
-    unsigned int pad[31];
+    unsigned int spin_limit;
+    unsigned int pad[30];
     GangLine sub[BAR_GROUPS];     // .v: arrivals of a group's blocks
     GangLine top;                 // .v: arrivals of the groups
     GangLine gen[BAR_GROUPS];     // .v: the group's copy of the generation
@@ -164,7 +164,7 @@ __device__ __forceinline__ bool gang_poll(Gang *gg, Ready &&ready)
 {
     unsigned int spins = 0;
     while (!ready()) {
-        if ((++spins & 63u) == 0u && (ld_dev(&gg->abort) || spins > SPIN_LIMIT)) {
+        if ((++spins & 63u) == 0u && (ld_dev(&gg->abort) || spins > gg->spin_limit)) {
             __hip_atomic_fetch_or(&gg->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
@@ -1033,8 +1033,9 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
     k ^= 1;
     const double bnorm = sqrt(bb.value);
     const double thresh = S.rtol * bnorm;
-    DotOut c0 = dot(S.r, S.r);
-    healthy = bb.ok && c0.ok;
+    DotOut c0 = {0.0, false, false};
+    if (bb.ok) c0 = dot(S.r, S.r);
+    healthy = c0.ok;
     double rr = c0.value;
     bool done = false;
     if (healthy && c0.all_perf) {
@@ -1145,7 +1146,9 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
         res->relres_est = bnorm > 0.0 ? sqrt(rr) / bnorm : 0.0;
         res->relres_true = relres_true;
     }
-    // leave the gang buffers clean and every block past its last use of them
+    // leave the gang buffers clean and every block past its last use of them;
+    // a gang that has given up leaves them to gang_reset, but this block's LDS
+    // counts, of rows that were never merged, to nobody
     if (healthy)
         gang_barrier_then(c, [&] {
             if ((int)threadIdx.x < c.groups) {
@@ -1153,6 +1156,8 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
                 st_dev(&gg->val[1][threadIdx.x].w, NO_VALUE);
             }
         });
+    else
+        for (int j = threadIdx.x; j < 4 * FQ; j += NT) L.h[j] = 0u;
     // the release is complete before this block enters the gang again
     vmem_drain();
     __syncthreads();
@@ -1160,7 +1165,7 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
 
 // Clears a gang's barrier, abort flag, values, partials and histogram buffers (plain
 // stores; used by a kernel of its own, before the launch that uses the gang).
-__device__ __forceinline__ void gang_reset(Gang *gg)
+__device__ __forceinline__ void gang_reset(Gang *gg, unsigned int spin_limit)
 {
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     for (int i = threadIdx.x; i < FQ; i += blockDim.x)
@@ -1180,6 +1185,7 @@ __device__ __forceinline__ void gang_reset(Gang *gg)
     if (threadIdx.x == 0) {
         gg->top.v = 0u;
         gg->abort = 0u;
+        gg->spin_limit = spin_limit;
     }
 }
 

@@ -57,6 +57,9 @@ struct FusedWs {
     unsigned int sub[ARRIVE_GROUPS][32];     // one 128-byte line per group
 };
 
+// Polls of a bounded wait before it gives up (over a minute).
+constexpr unsigned int SPIN_LIMIT = 1u << 26;
+
 // Control block in device memory, one per handle.
 struct Ws {
     unsigned long long hist[HIST_COPIES][W]; // pass-1 exponent histograms

@@ -39,6 +39,7 @@ struct qdot_handle {
     int spmv_blocks_per_cu = 8;      // SpMV grid
     int cg_blocks_per_cu = 2;        // single-system CG gang
     int power_scan_in_spmv = 0;      // power method: pass 1 inside the SpMV
+    unsigned int spin_limit = qd::SPIN_LIMIT; // polls of a CG gang's wait before it gives up
     void *cg = nullptr;              // persistent CG buffers
 
     // tile_skip: largest key slot of every 64-component tile, grown on demand

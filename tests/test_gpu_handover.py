@@ -85,3 +85,50 @@ def test_fp64_dots_in_a_row_batched(gang_max):
             for (_, _, x, *_), r, o in zip(systems, hh.cg_batched(systems), want):
                 assert (r["status"], r["iters"]) == (o["status"], o["iters"])
                 assert np.linalg.norm(x.cpu().numpy() - o["x"]) <= 1e-9 * np.linalg.norm(o["x"])
+
+
+@pytest.mark.parametrize("guard", [0, 1])
+def test_blocks_of_a_gang_that_gave_up_go_on_clean(guard, monkeypatch):
+    """A gang whose waits are given up at once (a spin limit of none, and one
+    block held up by a row as long as the matrix) reports it, and its blocks
+    then take qdot instances of the same launch: their results are those of a
+    launch without the system, byte for byte.  The next launch on the same
+    handle starts clean."""
+    import torch
+    n, gang = 65 * 1024, 65
+    rp, col, val = workloads.random_spd_csr(n, 2, 5)
+    r = 40 * 1024 + 7  # the long row, in the slice of block 40
+    rp, col, val = rp.astype(np.int64), col.astype(np.int64), val.astype(np.float64)
+    full = np.arange(n)
+    head, tail = slice(0, rp[r]), slice(rp[r + 1], None)
+    col2 = np.concatenate([col[head], full, col[tail]]).astype(np.int32)
+    val2 = np.concatenate([val[head], np.full(n, 1e-6), val[tail]])
+    rp2 = rp.copy()
+    rp2[r + 1:] += n - (rp[r + 1] - rp[r])
+    A = q.Csr(rp2.astype(np.int32), col2, val2)
+    b = torch.from_numpy(workloads.normal_vector(n, 2)).to("cuda:0")
+    lens = [100000 + 37 * (i % 50) for i in range(3000)] + [400000, 300001]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    # of the size of the system's residuals, so that counts left behind show
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(6)
+    x, y = (torch.randn(int(off[-1]), generator=g, dtype=torch.float64, device="cuda:0")
+            for _ in range(2))
+    off_d = torch.from_numpy(off).to("cuda:0")
+    tols = torch.full((len(lens),), 1e-6, dtype=torch.float64, device="cuda:0")
+    opt = [0, 0, 0, 0, guard]
+    res = [torch.zeros(len(lens) * q.RESULT_BYTES, dtype=torch.uint8, device="cuda:0")
+           for _ in range(2)]
+    with q.Qdot(0) as plain:
+        plain.batched_async(x, y, off_d, off, tols, res[0], opt=opt)
+        torch.cuda.synchronize()
+    monkeypatch.setenv("QDOT_SPIN_LIMIT", "0")
+    cg_out = torch.zeros(q.CG_RESULT_BYTES, dtype=torch.uint8, device="cuda:0")
+    with q.Qdot(0) as hh:
+        hh.set_solver_tune(cg_rows_per_block=1024, cg_gang_max=gang)
+        for _ in range(2):
+            system = (A, b, torch.zeros_like(b), 1e-8, 1e-8, 5, 1)
+            hh.batch_run_async(x, y, off_d, off, tols, res[1], [system], cg_out, opt=opt)
+            torch.cuda.synchronize()
+            assert q.parse_cg_results(cg_out)[0]["status"] == q.E_DEVICE
+            assert torch.equal(res[0], res[1])

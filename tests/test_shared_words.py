@@ -60,3 +60,15 @@ def test_gang_qdot_takes_a_value_back_behind_a_barrier_of_the_gang():
     barrier, which no block passes before it has read the other value."""
     body = _body("gang_qdot", "qdot_cg.hpp")
     assert body.index("gang_barrier_with<true>(") < body.index("gang_retract(")
+
+
+def test_a_block_whose_gang_gives_up_leaves_its_counts_clean():
+    """cg_solve is the one way out of a gang: where it has given up, the LDS
+    counts (which the launch's next item takes for zero) are cleared, after
+    the last place that fills them."""
+    body = _body("cg_solve", "qdot_cg.hpp")
+    clear = re.search(r"else\s+for \(int j = threadIdx.x; j < 4 \* FQ; j \+= NT\) L\.h\[j\] = 0u;",
+                      body)
+    assert clear
+    assert clear.start() > max(body.rindex("dot("), body.rindex("scan_pair("))
+    assert not re.search(r"\breturn;", body)
