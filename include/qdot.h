@@ -499,8 +499,13 @@ QDOT_API int32_t qdot_batched_plan(qdot_handle *h, const int64_t *host_offsets,
  * kernel launch.  Each CG system follows qdot_cg on that system alone (Alg.
  * 4 with the same stopping rule and the same inner products); it is solved
  * by a gang of blocks (one per cg_rows_per_block rows, at most cg_gang_max:
- * qdot_solver_tune) that meet at barriers,
- * gangs are formed before the qdot work items are handed out, largest
+ * qdot_solver_tune; more, up to an eighth of the blocks that the launch has
+ * resident, where the batch would leave some idle; never more than all of
+ * them) that meet at barriers.  A launch has at most one gang that waits for
+ * blocks, so at the default cg_gang_max up to 8 launches with systems may run
+ * at the same time on one GPU (each with its own handle and stream); beyond,
+ * their waiting gangs could hold every block until the spin limit.  Gangs are
+ * formed before the qdot work items are handed out, largest
  * system first.  dev_cg_out: device qdot_cg_result[S].  Planning happens on
  * the first call with a new layout (offsets and system descriptors,
  * compared by value) and is synchronous; later calls with the same layout

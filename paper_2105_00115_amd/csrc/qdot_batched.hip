@@ -33,6 +33,7 @@
 
 #include "qdot_select.hpp"
 #include "qdot_cg.hpp"
+#include "qdot_gang_shape.hpp"
 #include "qdot_handle.hpp"
 
 namespace qd {
@@ -49,7 +50,7 @@ constexpr int MAX_PLANS = 8;
 constexpr int BATCH_LE = 3840, BATCH_LE_ONEPASS = 2048;
 // A CG system of n rows gets a gang of ceil(n / batch_cg_rows) blocks, at
 // most batch_cg_gang_max (handle fields; defaults 16384 and 16), or more when
-// the batch would leave resident blocks idle (gang_shape).
+// the batch would leave resident blocks idle (qdot_gang_shape.hpp).
 
 enum : int { IT_P1 = 0, IT_SMALL = 1, IT_P2 = 2, IT_CG = 3 };
 
@@ -79,7 +80,7 @@ struct BState {
 struct BatchPlan {
     std::vector<int64_t> offsets;
     std::vector<qdot_cg_system> systems;
-    int B = 0, S = 0, accum = 0, n_items = 0, n_large = 0, n_p2 = 0, max_gang = 0;
+    int B = 0, S = 0, accum = 0, n_items = 0, n_large = 0, n_p2 = 0;
     double *ltab = nullptr;           // one-pass mode: per large instance W x S1_PIECES sums
     CgSys *sys = nullptr;             // S device descriptors
     Gang *gangs = nullptr;            // S gang states
@@ -379,9 +380,12 @@ __global__ __launch_bounds__(BLOCK) void k_gang_rearm(Gang *gangs, int S,
 // carries neither the CG solver's registers nor (two-pass) the one-pass
 // window's LDS: 128 VGPRs and 22 KB (four blocks per CU) for the two-pass
 // kernel, 168 VGPRs (three per CU) for the one-pass one, against two per CU
-// for the kernel that holds every path.
+// for those that hold the CG solver.  The guaranteed one of them spills 65
+// VGPRs for it; left at one block per CU, which shares out half as many blocks
+// among the gangs, 24 systems of sides 32 to 512 took 12.1 ms and 100 of 32 to
+// 256 8.3, against 5.9 and 5.0.
 template <bool GUARD, bool CG, int AM>
-__global__ __launch_bounds__(BLOCK, GUARD ? 1 : CG ? 2 : (AM ? 3 : 4)) void k_batch(const double *__restrict__ x,
+__global__ __launch_bounds__(BLOCK, CG ? 2 : GUARD ? 1 : (AM ? 3 : 4)) void k_batch(const double *__restrict__ x,
                                                  const double *__restrict__ y,
                                                  const int64_t *__restrict__ offsets,
                                                  const double *__restrict__ tols,
@@ -736,46 +740,73 @@ static bool same_system(const qdot_cg_system &a, const qdot_cg_system &b)
            a.use_qdot == b.use_qdot;
 }
 
-// Shape of the CG gangs of a batch: ceil(n / rows) blocks, at most `most`.
-struct GangShape {
-    int64_t rows;
-    int most;
-    int size(int64_t n) const
-    {
-        return (int)std::max<int64_t>(1, std::min<int64_t>(most, (n + rows - 1) / rows));
-    }
+// Arguments of one k_batch launch.
+struct BatchArgs {
+    const double *x, *y;
+    const int64_t *offsets;
+    const double *tols;
+    const BatchPlan *p;
+    qdot_result *out;
+    qdot_cg_result *cg_out;
+    int key_mode, score_mode, nonstrict;
 };
 
-// The tuned shape suits batches whose gangs fill the chip several times over.
-// Systems that it would give fewer blocks than are resident (two per CU)
-// share those out evenly: the fewest rows per block, a multiple of CHUNK, at
-// which all gangs are resident together.  24 Poisson systems of sides 32 to
-// 512, 60 iterations: 14.4 ms with the tuned shape (8192 rows, gangs of at
-// most 16, 185 blocks in all), 7.2 ms shared out.  GANG_SPREAD bounds a gang
-// because each launch has at most one gang that waits for blocks not yet
-// resident: up to 8 launches at the same time, on streams of their own, then
-// never hold all resident blocks in waiting gangs.
-constexpr int GANG_SPREAD = 64;
-
-static GangShape gang_shape(const qdot_handle *h, const qdot_cg_system *systems, int32_t S)
+template <bool GUARD, bool CG, int AM>
+static hipError_t batch_kernel_t(const BatchArgs &a, int grid, hipStream_t s, int *per_cu)
 {
-    const GangShape tuned = {h->batch_cg_rows, h->batch_cg_gang_max};
-    const int64_t resident = 2 * (int64_t)h->num_cus;
-    auto blocks = [&](const GangShape &g) {
-        int64_t b = 0;
-        for (int s = 0; s < S; s++) b += g.size(systems[s].A.n);
-        return b;
-    };
-    for (int64_t rows = CHUNK; rows < tuned.rows; rows += CHUNK) {
-        const GangShape g = {rows, std::max(GANG_SPREAD, tuned.most)};
-        if (blocks(g) <= resident) return g;
+    if (per_cu)
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_batch<GUARD, CG, AM>,
+                                                            BLOCK, 0);
+    const BatchPlan *p = a.p;
+    hipLaunchKernelGGL((k_batch<GUARD, CG, AM>), dim3(grid), dim3(BLOCK), 0, s, a.x, a.y,
+                       a.offsets, a.tols, p->items, p->n_items, p->large, p->hist, p->lut,
+                       p->partials, p->state, p->small_list, a.out, p->sys, p->gangs, a.cg_out,
+                       p->ltab, a.key_mode, a.score_mode, a.nonstrict);
+    return hipGetLastError();
+}
+
+// per_cu != nullptr: the occupancy query of the kernel the launch would use
+// (resident blocks per CU), no launch.
+static hipError_t batch_kernel(bool guard, bool cg, int accum, const BatchArgs &a, int grid,
+                               hipStream_t s, int *per_cu)
+{
+    if (guard)
+        return cg ? batch_kernel_t<true, true, 0>(a, grid, s, per_cu)
+                  : batch_kernel_t<true, false, 0>(a, grid, s, per_cu);
+    if (cg)
+        return accum ? batch_kernel_t<false, true, 1>(a, grid, s, per_cu)
+                     : batch_kernel_t<false, true, 0>(a, grid, s, per_cu);
+    return accum ? batch_kernel_t<false, false, 1>(a, grid, s, per_cu)
+                 : batch_kernel_t<false, false, 0>(a, grid, s, per_cu);
+}
+
+// Blocks of a launch with CG systems that are resident at once, whether it
+// runs in the guaranteed mode or not (a plan serves both): the grid holds
+// batch_blocks_per_cu per CU at most, and the kernels' registers and LDS may
+// hold fewer.
+static int32_t gang_residency(qdot_handle *h, int accum, int64_t *blocks)
+{
+    int per_cu = h->batch_blocks_per_cu;
+    for (const bool guard : {false, true}) {
+        if (guard && accum) continue;  // guard_mode 1 implies accum_mode 0
+        int k = 0;
+        const hipError_t e = batch_kernel(guard, true, accum, BatchArgs{}, 0, nullptr, &k);
+        if (e != hipSuccess) return hip_fail(h, e, "occupancy query");
+        per_cu = std::min(per_cu, k);
     }
-    return tuned;
+    if (per_cu < 1) return fail(h, QDOT_E_DEVICE, "the batched CG kernel cannot be resident");
+    *blocks = (int64_t)per_cu * h->num_cus;
+    return QDOT_OK;
 }
 
 static int32_t build_plan(qdot_handle *h, const int64_t *host_offsets, int32_t B,
                           const qdot_cg_system *systems, int32_t S, int accum, BatchPlan **out)
 {
+    int64_t resident = 0;
+    if (S > 0) {
+        const int32_t st = gang_residency(h, accum, &resident);
+        if (st != QDOT_OK) return st;
+    }
     BatchPlan *p = new BatchPlan();
     p->B = B;
     p->S = S;
@@ -797,10 +828,11 @@ static int32_t build_plan(qdot_handle *h, const int64_t *host_offsets, int32_t B
     std::iota(cg_order.begin(), cg_order.end(), 0);
     std::stable_sort(cg_order.begin(), cg_order.end(),
                      [&](int a, int c) { return systems[a].A.n > systems[c].A.n; });
-    const GangShape shape = gang_shape(h, systems, S);
+    const GangShape shape =
+        gang_shape([&](int s) { return systems[s].A.n; }, S,
+                   GangShape{h->batch_cg_rows, h->batch_cg_gang_max}, resident, CHUNK);
     for (int s : cg_order) {
         const int G = shape.size(systems[s].A.n);
-        p->max_gang = std::max(p->max_gang, G);
         for (int gb = 0; gb < G; gb++) items.push_back(BItem{IT_CG, s, G, gb, 0, 0});
     }
     std::vector<BLarge> lg(big.size());
@@ -824,8 +856,8 @@ static int32_t build_plan(qdot_handle *h, const int64_t *host_offsets, int32_t B
     // of 1e2 to 1e4 components in runs of SMALL_GROUP kept 45 blocks busy)
     int64_t small_cost = 0;
     for (int j : small) small_cost += len(j) + SMALL_COST0;
-    const int64_t resident = (int64_t)h->batch_blocks_per_cu * h->num_cus;
-    const int64_t budget = std::min(SMALL_GROUP, small_cost / resident);
+    const int64_t budget =
+        std::min(SMALL_GROUP, small_cost / ((int64_t)h->batch_blocks_per_cu * h->num_cus));
     for (size_t s0 = 0; s0 < small_list.size();) {
         size_t s1 = s0;
         int64_t cost = 0;
@@ -984,46 +1016,6 @@ static int32_t check_systems(qdot_handle *h, const qdot_cg_system *systems, int3
     return QDOT_OK;
 }
 
-// Arguments of one k_batch launch.
-struct BatchArgs {
-    const double *x, *y;
-    const int64_t *offsets;
-    const double *tols;
-    const BatchPlan *p;
-    qdot_result *out;
-    qdot_cg_result *cg_out;
-    int key_mode, score_mode, nonstrict;
-};
-
-template <bool GUARD, bool CG, int AM>
-static hipError_t batch_kernel_t(const BatchArgs &a, int grid, hipStream_t s, int *per_cu)
-{
-    if (per_cu)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, k_batch<GUARD, CG, AM>,
-                                                            BLOCK, 0);
-    const BatchPlan *p = a.p;
-    hipLaunchKernelGGL((k_batch<GUARD, CG, AM>), dim3(grid), dim3(BLOCK), 0, s, a.x, a.y,
-                       a.offsets, a.tols, p->items, p->n_items, p->large, p->hist, p->lut,
-                       p->partials, p->state, p->small_list, a.out, p->sys, p->gangs, a.cg_out,
-                       p->ltab, a.key_mode, a.score_mode, a.nonstrict);
-    return hipGetLastError();
-}
-
-// per_cu != nullptr: the occupancy query of the kernel the launch would use
-// (resident blocks per CU), no launch.
-static hipError_t batch_kernel(bool guard, bool cg, int accum, const BatchArgs &a, int grid,
-                               hipStream_t s, int *per_cu)
-{
-    if (guard)
-        return cg ? batch_kernel_t<true, true, 0>(a, grid, s, per_cu)
-                  : batch_kernel_t<true, false, 0>(a, grid, s, per_cu);
-    if (cg)
-        return accum ? batch_kernel_t<false, true, 1>(a, grid, s, per_cu)
-                     : batch_kernel_t<false, true, 0>(a, grid, s, per_cu);
-    return accum ? batch_kernel_t<false, false, 1>(a, grid, s, per_cu)
-                 : batch_kernel_t<false, false, 0>(a, grid, s, per_cu);
-}
-
 // Plans (when needed) and launches the work of one batch: B qdot instances
 // and S CG systems in one persistent launch.
 static int32_t batch_launch(qdot_handle *h, const double *x_cat, const double *y_cat,
@@ -1062,15 +1054,6 @@ static int32_t batch_launch(qdot_handle *h, const double *x_cat, const double *y
     const BatchArgs a = {x_cat, y_cat, offsets, tols, p, dev_out, dev_cg_out,
                          o.key_mode, o.score_mode, o.boundary_mode};
     const bool cg = S > 0;
-    if (p->max_gang > 0) {
-        // a gang waits for its own blocks only, so it needs that many
-        // blocks resident at once
-        int per_cu = 0;
-        hipError_t e = batch_kernel(o.guard_mode != 0, cg, accum, a, 0, nullptr, &per_cu);
-        if (e != hipSuccess) return hip_fail(h, e, "occupancy query");
-        if ((int64_t)per_cu * h->num_cus < p->max_gang)
-            return fail(h, QDOT_E_DEVICE, "CG gang larger than the resident blocks");
-    }
     hipStream_t s = (hipStream_t)stream;
     if (S > 0)
         hipLaunchKernelGGL(k_gang_rearm, dim3((unsigned)S), dim3(BLOCK), 0, s, p->gangs, S,
