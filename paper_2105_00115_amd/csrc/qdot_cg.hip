@@ -38,6 +38,7 @@ __global__ __launch_bounds__(NT, NT > BLOCK ? 4 : 2) void k_cg_gangs(const CgSys
     __syncthreads();
     const int g = blockIdx.x / G, gb = blockIdx.x % G;
     Gang *gg = gangs + g;
+    if (!gang_join(gg, G, &res[gang_sys[gang_sys_off[g]]].status)) return;
     auto run = [&](S1Lds *S1) {
         for (int s = gang_sys_off[g]; s < gang_sys_off[g + 1]; s++) {
             cg_solve<GUARD, NT, LE, ACC1>(sys[gang_sys[s]], gg, G, gb, key_mode, score_mode,
@@ -194,7 +195,10 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
         }
         e = hipMemsetAsync(d->s1tab, 0, sizeof(double) * CG_S1TAB, s);
     }
-    if (e == hipSuccess) {
+    // again while other launches hold the CUs: for as long as one gang would
+    // wait inside a launch
+    const unsigned int tries = 1u + h->spin_limit / JOIN_SPINS;
+    for (unsigned int t = 0; e == hipSuccess && t < tries; t++) {
         hipLaunchKernelGGL(k_gang_init, dim3(1), dim3(BLOCK), 0, s, d->gangs, 1,
                            h->spin_limit);
         if (acc1)
@@ -210,11 +214,17 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
                                0, s, d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res,
                                o.key_mode, o.score_mode, o.boundary_mode, (double *)nullptr);
         e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(out, d->res, sizeof(qdot_cg_result), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess || out->status != NOT_RESIDENT) break;
     }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out, d->res, sizeof(qdot_cg_result), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(h, e, "cg");
+    if (out->status == NOT_RESIDENT) {
+        *out = qdot_cg_result{};
+        out->status = QDOT_E_DEVICE;
+        return fail(h, QDOT_E_DEVICE, "the CG gang could not be resident together");
+    }
     if (out->status == QDOT_E_DEVICE) {
         // an abandoned solve may leave one-pass table entries behind
         if (d->s1tab && (hipMemsetAsync(d->s1tab, 0, sizeof(double) * CG_S1TAB, s) != hipSuccess ||

@@ -132,3 +132,50 @@ def test_blocks_of_a_gang_that_gave_up_go_on_clean(guard, monkeypatch):
             torch.cuda.synchronize()
             assert q.parse_cg_results(cg_out)[0]["status"] == q.E_DEVICE
             assert torch.equal(res[0], res[1])
+
+
+def _solves(handle, stream, side, seed, iters, rounds, opt, out):
+    import torch
+    A = q.Csr(*workloads.poisson2d_csr(side))
+    b = torch.from_numpy(workloads.normal_vector(A.n, seed)).to("cuda:0")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(rounds):
+            x = torch.zeros_like(b)
+            r = handle.cg(A, b, x, 1e-300, 1e-8, iters, 1, opt, stream=stream)
+            stream.synchronize()
+            out.append((r["status"], r["iters"], x.cpu().numpy().tobytes()))
+
+
+@pytest.mark.parametrize("sides,iters,rounds,opt",
+                         [((450, 450, 500), 20, 30, None),   # no two of them fit together
+                          ((1024, 450), 1500, 2, None),      # the first holds the chip for 75 ms
+                          ((700, 450), 20, 15, [0, 0, 0, 0, 1])])
+def test_solves_on_several_streams(sides, iters, rounds, opt):
+    """Solves on streams of their own at the same time, each with its handle
+    and thread, whose gangs would together need more CUs than there are: every
+    one gives what it gives alone, byte for byte."""
+    import threading
+    import torch
+    handles = [q.Qdot(0) for _ in sides]
+    streams = [torch.cuda.Stream() for _ in sides]
+    try:
+        want = []
+        for k, side in enumerate(sides):
+            one = []
+            _solves(handles[k], streams[k], side, k, iters, 1, opt, one)
+            assert one[0][:2] == (q.E_MAXIT, iters)
+            want.append(one[0])
+        got = [[] for _ in sides]
+        threads = [threading.Thread(target=_solves, args=(handles[k], streams[k], side, k, iters,
+                                                          rounds, opt, got[k]))
+                   for k, side in enumerate(sides)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for k in range(len(sides)):
+            assert len(got[k]) == rounds and all(r == want[k] for r in got[k])
+    finally:
+        for handle in handles:
+            handle.close()

@@ -72,3 +72,15 @@ def test_a_block_whose_gang_gives_up_leaves_its_counts_clean():
     assert clear
     assert clear.start() > max(body.rindex("dot("), body.rindex("scan_pair("))
     assert not re.search(r"\breturn;", body)
+
+
+def test_a_gang_with_a_launch_of_its_own_comes_together_before_it_begins():
+    """Another solve's launch may hold CUs that the gang waits for, and the
+    other way round: the blocks meet first (a bounded wait that all of them
+    leave the same way), before any of them stores a result."""
+    body = _body("k_cg_gangs", "qdot_cg.hip")
+    assert body.index("gang_join(") < body.index("cg_solve<")
+    join = _body("gang_join", "qdot_cg.hpp")
+    assert join.count("compare_exchange") == 1 and "spins >= limit" in join
+    reset = _body("gang_reset", "qdot_cg.hpp")
+    assert "gg->join.v = 0u;" in reset and "gg->verdict.v = 0u;" in reset
