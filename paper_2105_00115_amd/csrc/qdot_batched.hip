@@ -378,12 +378,13 @@ __global__ __launch_bounds__(BLOCK) void k_gang_rearm(Gang *gangs, int S,
 // CG: the work list may hold CG items.  AM: the qdot instances' accum_mode.
 // Each combination is its own kernel, so a launch of qdot instances alone
 // carries neither the CG solver's registers nor (two-pass) the one-pass
-// window's LDS: 128 VGPRs and 22 KB (four blocks per CU) for the two-pass
-// kernel, 168 VGPRs (three per CU) for the one-pass one, against two per CU
-// for those that hold the CG solver.  The guaranteed one of them spills 65
-// VGPRs for it; left at one block per CU, which shares out half as many blocks
-// among the gangs, 24 systems of sides 32 to 512 took 12.1 ms and 100 of 32 to
-// 256 8.3, against 5.9 and 5.0.
+// window's LDS: 128 VGPRs (5 more spilled) and 22 KB (four blocks per CU) for
+// the two-pass kernel, 168 VGPRs (three per CU) for the one-pass one, against
+// two per CU for those that hold the CG solver (256, and 8 spilled in the
+// two-pass one).  The guaranteed one of them spills 65 for that; left at one
+// block per CU, which shares out half as many blocks among the gangs, 24
+// systems of sides 32 to 512 took 12.1 ms and 100 of 32 to 256 8.3, against 5.9
+// and 5.0.
 template <bool GUARD, bool CG, int AM>
 __global__ __launch_bounds__(BLOCK, CG ? 2 : GUARD ? 1 : (AM ? 3 : 4)) void k_batch(const double *__restrict__ x,
                                                  const double *__restrict__ y,

@@ -14,7 +14,8 @@ namespace qd {
 // The two-pass gang: one block of 1024 threads per CU, so that few blocks meet
 // at a barrier and the block's slice has the CU's whole LDS (CG_ENTRIES of its
 // matrix entries stay there, qdot_cg.hpp).  Poisson 1024^2, per iteration:
-// 53.7 us, 56.3 with 512 threads.  The guaranteed and the one-pass mode hold
+// 53.7 us, 56.3 with 512 threads, when these were chosen; 50.2 now, though 67
+// of the 128 registers that 1024 threads leave are spilled.  The guaranteed and the one-pass mode hold
 // too many registers for it and run two blocks of BLOCK threads per CU.
 constexpr int CG_THREADS = 1024;
 constexpr int CG_ENTRIES = 10240;

@@ -866,8 +866,9 @@ __device__ __forceinline__ DotOut gang_dot64(const double *a, const double *bv, 
 // resident), per iteration with the two-pass qdot: 64 us with every entry
 // read behind the barrier (the SpMV 20.5 of them), 66 with the products of
 // coalesced entries staged through LDS, 53.7 with the resident rows; with the
-// gathered sums 51.4, and 50.1 with the row ahead.  Two rows per thread in
-// flight at once spilled: 69.8.
+// gathered sums 51.4, and 50.1 with the row ahead (this form spills 67 of its
+// 128 VGPRs, 272 bytes of scratch per lane).  Two rows per thread in flight at
+// once spilled more: 69.8.
 // The batch of 24 systems (64 blocks of 256 threads for the largest, 4096
 // rows each, a fifth of them resident): 4.66 ms, with the row ahead 3.82.
 // ---------------------------------------------------------------------------

@@ -24,7 +24,8 @@
 // Per call, back to back (four kernels -> here): 1000 components 20 -> 11 us
 // (one block, 6.4 us in the kernel), 1e5 24.0 -> 13.8, 1e6 27.5 -> 18.0,
 // guaranteed mode on 1e6 36.6 -> 20.9 (eight launches -> three), 1e7 72.4 ->
-// 62.1, 2^27 695 -> 685, 5e7 floats 168 -> 164.
+// 62.1.  Past 128 MiB per vector the guaranteed mode alone takes this form
+// (the default mode below: k_spec_sweep).
 //
 // Classes, leaves and tile trees are those of the four-kernel chain, and so is
 // the order of every FP64 sum where the launch shapes are the same (long
@@ -280,10 +281,8 @@ __device__ __forceinline__ void sel_sweep(const T *__restrict__ x, const T *__re
         } else if (copies == 1) {
 #pragma unroll
             for (int k = 0; k < K; k++) v[k] = quad(0, k);
-        } else if (copies == 2) {
-#pragma unroll
-            for (int k = 0; k < K; k++) v[k] = plus(quad(0, k), quad(1, k));
-        } else {
+        } else {  // FH_COPIES (fused_copies)
+            static_assert(FH_COPIES == 4, "four copies");
 #pragma unroll
             for (int k = 0; k < K; k++)
                 v[k] = plus(plus(quad(0, k), quad(1, k)), plus(quad(2, k), quad(3, k)));
@@ -486,13 +485,13 @@ __device__ __forceinline__ void count_runs(const T *__restrict__ x, const T *__r
     constexpr unsigned int PER = 4 / U;  // groups of a run
     const unsigned int runs = (unsigned int)((n + SAMPLE_RUN - 1) / SAMPLE_RUN);
     const int64_t past = n + SAMPLE_RUN;  // a stride that ends the walk
-    unsigned int sg = 0;
+    unsigned int signs = 0;  // not needed here: no guard follows
     for (unsigned int i = blockIdx.x;; i += gridDim.x) {
         const unsigned int r = run(i / PER);
         if (r >= runs) break;
         stream_strided<VEC, U>(x, y, r * SAMPLE_RUN + (i % PER) * ((int64_t)CHUNK * U), past, n,
                                [&](const T *xv, const T *yv, int64_t, int lim) {
-                                   count4(xv, yv, lim, key_mode, h, sg);
+                                   count4(xv, yv, lim, key_mode, h, signs);
                                });
     }
 }
