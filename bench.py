@@ -30,7 +30,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "qdot Gelem/s & % HBM peak vs FP64 dot at rel err<=1e-6; CG iteration count"
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_acc_single_qdot_2p27_traffic.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "single_qdot_2p27_traffic.json")
 
 
 def log(msg):

@@ -537,8 +537,8 @@ QDOT_API int32_t qdot_cg_batched(qdot_handle *h, const qdot_cg_system *systems, 
 
 /* y = A x for a CSR matrix (rows summed in stored order, each product and
  * sum one FP64 rounding).  col entries must lie in [0, n); rows of any
- * length are accepted.  The grid holds up to 8 blocks per CU (environment
- * variable QDOT_SPMV_BPC, 1..16, overrides it).  Async. */
+ * length are accepted.  The grid holds up to spmv_blocks_per_cu blocks per CU
+ * (qdot_solver_tune).  Async. */
 QDOT_API int32_t qdot_spmv_async(qdot_handle *h, const qdot_csr *A, const double *x,
                         double *y, void *stream);
 
@@ -552,8 +552,11 @@ QDOT_API int32_t qdot_spmv_async(qdot_handle *h, const qdot_csr *A, const double
  * The whole solve is one persistent launch of one block per CU, or with
  * accum_mode 1 or guard_mode 1 up to two smaller ones
  * (as many as can be resident together; at most 512, at least 1024 rows
- * per block; environment variable QDOT_CG_BLOCKS caps the count).  A gang
- * barrier that does not complete within its spin limit ends the solve with
+ * per block).  Solves on several streams may run at the same time, each with
+ * its own handle: one whose blocks do not come together within some 20 ms,
+ * because others hold the CUs, leaves the GPU and is launched again.  A gang
+ * barrier that does not complete within its spin limit, or blocks that do not
+ * come together for as long, end the solve with
  * QDOT_E_DEVICE.  guard_mode 1 runs the guaranteed mode on every qdot of
  * the solve (same decisions, flags, lower bound and passes as qdot_async; a
  * reselected product costs one more sweep of the gang's rows and one more

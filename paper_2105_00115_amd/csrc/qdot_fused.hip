@@ -860,8 +860,8 @@ constexpr int64_t WIDE_MAX = (int64_t)CHUNK * 512;
 // made for it (5e7 products 309 us, 172 when it stands).  The sample has at
 // least SPEC_SAMPLE components, less than twice that: the top bin of
 // 10**U[-20, 20] products then holds 91 or more.  On 24 draws each at 5e7
-// (three tolerances), 5 * 2^19 components guessed 21 rightly, 2^22 and 2^23
-// components 23, and 2^23 took 15 us more.
+// (three tolerances, by the top and t alone), 5 * 2^19 components guessed 21
+// rightly, 2^22 and 2^23 components 23, and 2^23 took 15 us more.
 constexpr int64_t SPEC_MIN_BYTES = (int64_t)1 << 27;
 constexpr int64_t SPEC_SAMPLE = (int64_t)1 << 22;
 

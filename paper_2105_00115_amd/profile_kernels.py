@@ -5,8 +5,10 @@ Runs, in this order, on cuda:0:
 1. a 256 MiB ``torch`` copy (256 MiB read, 256 MiB written), whose
    FETCH_SIZE / WRITE_SIZE give the scale factors of the byte counters;
 2. the single qdot on the throughput workload (n = 2^27 FP64 components
-   +-10^U[-20,20], tol 1e-6): ``steps`` calls of the two-pass mode, of the
-   one-pass mode and of the FP64 dot;
+   +-10^U[-20,20], tol 1e-6): ``steps`` calls of the default mode (the
+   classes guessed from a sample), of the one-pass mode, of the FP64 dot, of
+   the guaranteed mode (two passes) and, on the same vectors as floats, of the
+   default mode;
 3. CG on the 2D Poisson matrix 1024^2 (qdot tol 1e-8, stop at 1e-10) with
    the two-pass qdot, the FP64 dot and the one-pass qdot, one solve each;
 4. the power method on the 3D Laplacian 128^3, ``power_iters`` iterations
@@ -64,6 +66,11 @@ def main(argv=None):
         h.qdot_async(x, y, tol, out, opt=[0, 0, 0, 1])
     for _ in range(a.steps):
         h.fp64_dot_async(x, y, d_out)
+    for _ in range(a.steps):
+        h.qdot_async(x, y, tol, out, opt=[0, 0, 0, 0, 1])
+    x, y = x.float(), y.float()
+    for _ in range(a.steps):
+        h.qdot_f32_async(x, y, tol, out)
     torch.cuda.synchronize()
     del x, y
 

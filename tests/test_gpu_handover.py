@@ -179,3 +179,16 @@ def test_solves_on_several_streams(sides, iters, rounds, opt):
     finally:
         for handle in handles:
             handle.close()
+
+
+@pytest.mark.parametrize("use", [0, 1])
+def test_a_system_of_one_row(h, use):
+    """3 x = 6: one step from 0 gives 2 (each product and quotient rounds
+    once), and the residual is 0."""
+    import torch
+    A = q.Csr(np.array([0, 1], np.int32), np.zeros(1, np.int32), np.full(1, 3.0))
+    b = torch.full((1,), 6.0, dtype=torch.float64, device="cuda:0")
+    x = torch.zeros_like(b)
+    r = h.cg(A, b, x, 1e-12, 1e-10, 12, use)
+    assert (r["status"], r["iters"], float(x)) == (q.OK, 1, 2.0)
+    assert r["relres_true"] <= 1e-15
