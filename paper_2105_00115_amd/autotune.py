@@ -23,7 +23,7 @@ Long vectors (the last bucket) count and sum in one kernel by default, behind a
 sample whose grid is fixed, so there the scan's shape is timed on the
 guaranteed mode, which scans the whole, and the accumulate shape on the default
 mode.  The form of the accumulate pass and the threads per block choose between
-the routes; the histogram copies belong to the four-kernel one, and are swept
+the routes; the histogram copies belong to the four-kernel one, and are timed
 there alone.
 
 Solvers and batched launch, each on the benchmark workload it serves:
@@ -173,11 +173,11 @@ def tune(reps: int = 20, seed: int = 7, tol: float = 1e-6, log=print, buckets=No
             for hc in HIST_COPIES:
                 for nt in BLOCK_THREADS:
                     cfg = best[:6] + (af, hc, nt)
-                    if (af, nt) == (0, 256) and hc != 8:
-                        continue
-                    cand[cfg] = _time_config(h, x, y, tol, out, cfg, reps)
                     _check_same(h, x, y, tol, cfg, ref)
                     checked += 1
+                    if (af, nt) == (0, 256) and hc != 8:
+                        continue  # the copies play no part in this form
+                    cand[cfg] = _time_config(h, x, y, tol, out, cfg, reps)
         challenger = min(cand, key=lambda c: sum(cand[c]))
         if challenger != base:
             tb = tc = 0.0
