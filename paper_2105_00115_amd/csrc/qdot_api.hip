@@ -282,9 +282,11 @@ int32_t qdot_create(qdot_handle **out, int32_t device)
         return QDOT_E_NOMEM;
     }
     if (const char *p = std::getenv("QDOT_TUNE_FILE")) (void)qdot_load_tune(h, p);
-    if (const char *p = std::getenv("QDOT_SPIN_LIMIT"))
-        h->spin_limit = (unsigned int)std::min<unsigned long long>(std::strtoull(p, nullptr, 10),
-                                                                   SPIN_LIMIT);
+    if (const char *p = std::getenv("QDOT_SPIN_LIMIT")) {
+        char *end = nullptr;
+        const unsigned long long v = std::strtoull(p, &end, 10);
+        if (end != p) h->spin_limit = (unsigned int)std::min<unsigned long long>(v, SPIN_LIMIT);
+    }
     *out = h;
     return QDOT_OK;
 }
