@@ -554,7 +554,8 @@ QDOT_API int32_t qdot_spmv_async(qdot_handle *h, const qdot_csr *A, const double
  * (as many as can be resident together; at most 512, at least 1024 rows
  * per block).  Solves on several streams may run at the same time, each with
  * its own handle: one whose blocks do not come together within some 20 ms,
- * because others hold the CUs, leaves the GPU and is launched again.  A gang
+ * because others hold the CUs, leaves the GPU and is launched again (and waits
+ * twice as long each time).  A gang
  * barrier that does not complete within its spin limit, or blocks that do not
  * come together for as long, end the solve with
  * QDOT_E_DEVICE.  guard_mode 1 runs the guaranteed mode on every qdot of

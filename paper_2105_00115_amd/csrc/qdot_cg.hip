@@ -55,11 +55,11 @@ __global__ __launch_bounds__(NT, NT > BLOCK ? 4 : 2) void k_cg_gangs(const CgSys
     }
 }
 
-__global__ void k_gang_init(Gang *gangs, int n, unsigned int spin_limit)
+__global__ void k_gang_init(Gang *gangs, int n, unsigned int spin_limit, unsigned int join_spins)
 {
     const int g = blockIdx.x;
     if (g >= n) return;
-    gang_reset(gangs + g, spin_limit);
+    gang_reset(gangs + g, spin_limit, join_spins);
 }
 
 // ---------------------------------------------------------------------------
@@ -196,12 +196,12 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
         }
         e = hipMemsetAsync(d->s1tab, 0, sizeof(double) * CG_S1TAB, s);
     }
-    // again while other launches hold the CUs: for as long as one gang would
-    // wait inside a launch
-    const unsigned int tries = 1u + h->spin_limit / JOIN_SPINS;
-    for (unsigned int t = 0; e == hipSuccess && t < tries; t++) {
+    // again while other launches hold the CUs, until it has waited as long in
+    // one launch as any gang does
+    for (unsigned int join = std::min(JOIN_SPINS, h->spin_limit); e == hipSuccess;
+         join = std::min(2u * join, h->spin_limit)) {
         hipLaunchKernelGGL(k_gang_init, dim3(1), dim3(BLOCK), 0, s, d->gangs, 1,
-                           h->spin_limit);
+                           h->spin_limit, join);
         if (acc1)
             hipLaunchKernelGGL((k_cg_gangs<false, true, BLOCK>), dim3(G), dim3(BLOCK), 0, s,
                                d->sys, d->gsys, d->gsys + 1, d->gangs, G, d->res, o.key_mode,
@@ -218,7 +218,7 @@ int32_t qdot_cg(qdot_handle *h, const qdot_csr *A, const double *b, double *x, d
         if (e == hipSuccess)
             e = hipMemcpyAsync(out, d->res, sizeof(qdot_cg_result), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess || out->status != NOT_RESIDENT) break;
+        if (e != hipSuccess || out->status != NOT_RESIDENT || join == h->spin_limit) break;
     }
     if (e != hipSuccess) return hip_fail(h, e, "cg");
     if (out->status == NOT_RESIDENT) {

@@ -78,7 +78,8 @@ constexpr unsigned long long NO_VALUE = 0x7ff4dead00c0ffeeull;
 struct Gang {
     unsigned int abort;
     unsigned int spin_limit;
-    unsigned int pad[30];
+    unsigned int join_spins;      // polls of gang_join
+    unsigned int pad[29];
     GangLine join;                // .v: blocks that are on the chip (gang_join)
     GangLine verdict;             // .v: what became of that
     GangLine sub[BAR_GROUPS];     // .v: arrivals of a group's blocks
@@ -99,10 +100,12 @@ struct Gang {
 // A gang that has a launch of its own first waits until all of its blocks are
 // on the chip: another launch of this kind (a solve on another stream) may
 // have taken some CUs in between, and each would then wait for the CUs that
-// the other holds.  A gang that has not come together after JOIN_SPINS polls
-// (some 20 ms) leaves the chip again, before it has touched anything, and the
-// host launches it anew.  `status` gets NOT_RESIDENT then.  The verdict is
-// given once: by the last block to join, or by the first to give up.
+// the other holds.  A gang that has not come together after join_spins polls
+// leaves the chip again, before it has touched anything, and the host launches
+// it anew: JOIN_SPINS of them (some 20 ms) at first, and twice as many each
+// time, so that long blocks of other work, which a gang has to wait out, hold
+// it up no longer than if it had stayed.  `status` gets NOT_RESIDENT then.  The
+// verdict is given once: by the last block to join, or by the first to give up.
 // 0.2 % of a solve of 60 iterations.
 constexpr unsigned int JOIN_SPINS = 1u << 14;
 constexpr unsigned int JOIN_GO = 1u, JOIN_LEAVE = 2u;
@@ -125,7 +128,7 @@ __device__ __forceinline__ bool gang_join(Gang *gg, int G, int32_t *status)
                 1u == (unsigned)G) {
             give(JOIN_GO);
         } else {
-            const unsigned int limit = min(JOIN_SPINS, gg->spin_limit);
+            const unsigned int limit = gg->join_spins;
             for (unsigned int spins = 0; (v = ld_dev(&gg->verdict.v)) == 0u; spins++) {
                 if (spins >= limit) {
                     give(JOIN_LEAVE);
@@ -1212,7 +1215,8 @@ __device__ __forceinline__ void cg_solve(const CgSys &S, Gang *gg, int G, int gb
 
 // Clears a gang's barrier, abort flag, values, partials and histogram buffers (plain
 // stores; used by a kernel of its own, before the launch that uses the gang).
-__device__ __forceinline__ void gang_reset(Gang *gg, unsigned int spin_limit)
+__device__ __forceinline__ void gang_reset(Gang *gg, unsigned int spin_limit,
+                                           unsigned int join_spins = 0u)
 {
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     for (int i = threadIdx.x; i < FQ; i += blockDim.x)
@@ -1235,6 +1239,7 @@ __device__ __forceinline__ void gang_reset(Gang *gg, unsigned int spin_limit)
         gg->top.v = 0u;
         gg->abort = 0u;
         gg->spin_limit = spin_limit;
+        gg->join_spins = join_spins;
     }
 }
 
